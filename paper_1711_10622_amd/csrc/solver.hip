@@ -116,9 +116,13 @@ Layout layout(int32_t n, int32_t m, uint32_t flags, const AmgDev *amg = nullptr)
     L.ctl = take(sizeof(Ctl));
     L.kry64 = take(sizeof(Kry<double>));
     L.kry32 = take(sizeof(Kry<float>));
-    L.tickets = take(sizeof(unsigned) * (kGroups + 1));
+    // the partial sums have room for kMaxDots dots of kMaxM columns, more than
+    // any reduction has; the ticket counters' lines are taken out of it
     const size_t V = static_cast<size_t>(kMaxDots) * kMaxM;
-    L.part = take(sizeof(double) * V * static_cast<size_t>(max_grid()));
+    static_assert(sizeof(unsigned) * kTicketStride % kAlign == 0, "a counter fills whole lines");
+    L.tickets = take(sizeof(unsigned) * kTicketStride * (kGroups + 1));
+    L.part = take(sizeof(double) * V * static_cast<size_t>(max_grid()) -
+                  sizeof(unsigned) * kTicketStride * kGroups);
     L.gpart = take(sizeof(double) * V * kGroups);
     const size_t blk64 = sizeof(double) * static_cast<size_t>(n) * m;
     const size_t blk32 = sizeof(float) * static_cast<size_t>(n) * m;
@@ -526,7 +530,8 @@ mrhs_status Engine::reset()
     for (int c = 0; c < kMaxM; ++c)
         col_steps_[c] = 0;
     waited_ = 0;
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s_, tickets_, kGroups + 1, 0u);
+    constexpr int kTickets = kTicketStride * (kGroups + 1);
+    hipLaunchKernelGGL(k_fill_u32, dim3((kTickets + 255) / 256), dim3(256), 0, s_, tickets_, kTickets, 0u);
     hipLaunchKernelGGL(k_ctl_reset, dim3(1), dim3(64), 0, s_, c_.ctl, mixed_ ? MODE_INNER : MODE_F64, tol_in_,
                        max_outer_, A_.n, stag_window_);
     MRHS_HIP(hipGetLastError());
