@@ -645,13 +645,14 @@ int32_t median_reach(const amg::HostCsr &A)
     return reach[A.nr / 2];
 }
 
-// Small levels with long rows (the coarse Galerkin levels, 30-90 nonzeros
-// per row, and the coarsest dense inverse) take the one-wave-per-row product:
-// the tiled one would run them on a few workgroups with long serial row
-// chains.  Large levels keep the tiled product: with ~15 nonzeros per row one
-// row per wave leaves most gather slots empty (measured on the 12.6M-row
-// channel's first coarse level, 6.3M rows: 1070 -> 1371 us per sweep).
-constexpr double kSplitRowNnz = 12.0;
+// Levels of fewer rows than this take the short-chain product
+// (gspmv_rows_split), their transfers and the coarsest dense inverse too: the
+// tiled one would stage a few tiles and walk the long rows of a coarse
+// Galerkin operator (15-90 entries) on a few workgroups.  524k-row channel, 7
+// levels of 524,288 to 197 rows: with the line at 400,000 rows (the level of
+// 262,144 rows on it too) a V-cycle takes 415 us at m = 1 and 918 us at m = 16
+// against 388 and 801 us; with only levels of 12 and more entries per row on
+// it, 395 and 807 us.
 constexpr int32_t kSplitMaxRows = 131072;
 
 CsrView<double> upload_csr(mrhs_amg_s *H, const amg::HostCsr &C, const std::vector<double> *vals, int32_t reach,
@@ -663,7 +664,8 @@ CsrView<double> upload_csr(mrhs_amg_s *H, const amg::HostCsr &C, const std::vect
     v.va = upload(H, (vals ? vals : &C.va)->data(), C.va.size(), kPadElems, err);
     v.n = C.nr;
     v.reach = reach;
-    v.split = C.nr > 0 && C.nr < kSplitMaxRows && static_cast<double>(C.nnz()) >= kSplitRowNnz * C.nr;
+    if (C.nr > 0 && C.nr < kSplitMaxRows)
+        v.split = std::max(1, static_cast<int32_t>(C.nnz() / C.nr));
     return v;
 }
 
@@ -869,8 +871,9 @@ MRHS_API mrhs_status amg_create(mrhs_csr A, double theta, int32_t max_coarse, in
             H->cf.push_back(hl.cf);
         }
         // the tiled products of A_l and A_l D_l1^-1 read codes where the
-        // level's operator has a dictionary form (MRHS_CSR_DICT=0: never)
-        if (use_dict && !d.A.split && hl.A.nnz() > 0 && e == hipSuccess) {
+        // level's operator has a dictionary form (MRHS_CSR_DICT=0: never);
+        // the iteration's own products with A_0 are tiled at every size
+        if (use_dict && (l == 0 || !d.A.split) && hl.A.nnz() > 0 && e == hipSuccess) {
             dict::Offsets offs;
             dict::offsets(hl.A.nr, hl.A.rp.data(), hl.A.ci.data(), offs);
             std::vector<int32_t> otab(offs.set.keys.begin(), offs.set.keys.end());

@@ -286,26 +286,32 @@ struct TileRange {
     }
 };
 
-__device__ __forceinline__ TileRange tile_range(int32_t ntiles, int32_t P = 0, int32_t C = 1)
+// The tiles of a kernel over n rows and their order, worked out by the host:
+// the divisions it takes cost a microsecond and more at the head of every
+// kernel.
+struct TilePlan {
+    int32_t passes, ntiles;      // passes per tile, tiles
+    int32_t P = 0, C = 1;        // plane mode: tiles per plane, chunks (C divides P)
+    int32_t planes = 0;
+};
+
+__device__ __forceinline__ TileRange tile_range(const TilePlan &p)
 {
 #if !MRHS_XCD_GROUPS
-    return {static_cast<int32_t>(blockIdx.x), ntiles, static_cast<int32_t>(gridDim.x), 0, 0, 1, 1, 1};
+    return {static_cast<int32_t>(blockIdx.x), p.ntiles, static_cast<int32_t>(gridDim.x), 0, 0, 1, 1, 1};
 #endif
     const int b = blockIdx.x;
     const int grp = b % kGroups;
     const int q = b / kGroups;
     const int gx = gridDim.x / kGroups;
-    if (P) {
-        if (P % C != 0 || P / C < 2 * kGroups)
-            C = 1;
-        const int32_t W = P / C;
+    if (p.P) {
+        const int32_t W = p.C > 1 ? p.P / p.C : p.P;
         const int32_t lo = W * grp / kGroups;
         const int32_t cg = W * (grp + 1) / kGroups - lo;
-        const int32_t planes = (ntiles + P - 1) / P;
-        return {q, C * planes * cg, gx, P, lo, cg, W, planes * cg};
+        return {q, p.C * p.planes * cg, gx, p.P, lo, cg, W, p.planes * cg};
     }
-    const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(ntiles) * grp / kGroups);
-    const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(ntiles) * (grp + 1) / kGroups);
+    const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(p.ntiles) * grp / kGroups);
+    const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(p.ntiles) * (grp + 1) / kGroups);
     return {lo + q, hi, gx, 0, 0, 1, 1, 1};
 }
 
@@ -314,7 +320,7 @@ __device__ __forceinline__ TileRange tile_range(int32_t ntiles, int32_t P = 0, i
 // the largest column - row offset) rounded to whole tiles, used when every
 // group gets at least two tiles of each plane and there are at least four
 // planes.
-__device__ __forceinline__ int32_t plane_tiles(int32_t reach, int32_t tile_rows, int32_t ntiles)
+inline int32_t plane_tiles(int32_t reach, int32_t tile_rows, int32_t ntiles)
 {
     const int32_t P = (reach + tile_rows / 2) / tile_rows;
     return (P >= 2 * kGroups && ntiles >= 4 * P) ? P : 0;
@@ -339,8 +345,7 @@ __device__ __forceinline__ int32_t plane_tiles(int32_t reach, int32_t tile_rows,
 constexpr int32_t kPlaneShareBytes = MRHS_PLANE_SHARE_KB << 10;
 constexpr int32_t kMinChunkTiles = MRHS_PLANE_MIN_CHUNK;
 
-__device__ __forceinline__ int32_t plane_chunks(int32_t P, int32_t reach, int32_t tile_rows,
-                                                int32_t block_bytes_per_tile)
+inline int32_t plane_chunks(int32_t P, int32_t reach, int32_t tile_rows, int32_t block_bytes_per_tile)
 {
 #if MRHS_PLANE_CHUNKS
     return MRHS_PLANE_CHUNKS;
@@ -353,6 +358,22 @@ __device__ __forceinline__ int32_t plane_chunks(int32_t P, int32_t reach, int32_
         if (P % C == 0)
             return C;
     return 1;
+}
+
+// Plan of a kernel over n rows in tiles of passes * pass_rows rows; reach > 0
+// allows plane mode, for a product that moves row_bytes of block rows per row.
+inline TilePlan tile_plan(int32_t n, int passes, int pass_rows, int32_t reach = 0, int32_t row_bytes = 0)
+{
+    const int32_t rows = passes * pass_rows;
+    TilePlan p{passes, static_cast<int32_t>((static_cast<int64_t>(n) + rows - 1) / rows)};
+    p.P = plane_tiles(reach, rows, p.ntiles);
+    if (p.P) {
+        p.C = plane_chunks(p.P, reach, rows, row_bytes * rows);
+        if (p.P % p.C != 0 || p.P / p.C < 2 * kGroups)
+            p.C = 1;
+        p.planes = (p.ntiles + p.P - 1) / p.P;
+    }
+    return p;
 }
 
 // ---- matrix view ----------------------------------------------------------------
@@ -375,7 +396,7 @@ struct CsrView {
     const T *__restrict__ va;
     int32_t n;
     int32_t reach;  // median over rows of the largest forward column offset
-    int32_t split;  // nonzero: long rows, one wave per row (gspmv_rows_split)
+    int32_t split;  // nonzero: few rows, of this many entries on average (gspmv_rows_split)
     // dictionary form (gspmv_tiles only; null code and ccode: the plain arrays)
     const uint16_t *__restrict__ code = nullptr;   // [nnz + 8]
     const int32_t *__restrict__ otab = nullptr;    // [noffs]
@@ -534,9 +555,9 @@ struct pre_of<Op, true> {
     using type = typename Op::Pre;
 };
 
-// Ops that set kLongRows = true may run on the one-wave-per-row product
-// (gspmv_rows_split) when their matrix has long rows; the others always use
-// the tiled one, which is correct for any matrix.
+// Ops that set kLongRows = true may run on gspmv_rows_split when their matrix
+// is marked for it (CsrView::split); the others always use the tiled product,
+// which is correct for any matrix.
 template <class Op, class = void>
 struct long_rows_ok : std::false_type {};
 template <class Op>
@@ -633,9 +654,10 @@ struct TileLds {
 // 8-aligned index zb <= z0; the code array carries 8 codes of padding).
 template <typename T, int M, class Op>
 __device__ __forceinline__ void gspmv_tiles_dict(const CsrView<T> &A, const Op &op,
-                                                 Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, int32_t *s_rp,
+                                                 Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan, int32_t *s_rp,
                                                  unsigned char *s_buf)
 {
+    const int tr_rows = plan.passes * Shape<T, M>::RPP;
     using S = Shape<T, M>;
     using LD = TileLds<T, M>;
     using I4 = int __attribute__((ext_vector_type(4)));
@@ -654,17 +676,14 @@ __device__ __forceinline__ void gspmv_tiles_dict(const CsrView<T> &A, const Op &
     // (visible after the first tile's barrier)
     const int ob = A.ob;
     const uint32_t omask = (1u << ob) - 1u;
-    const int32_t ntiles = static_cast<int32_t>((static_cast<int64_t>(A.n) + S::TR - 1) / S::TR);
-    const int32_t P = plane_tiles(A.reach, S::TR, ntiles);
-    constexpr int32_t kBlockBytes = (gathered_blocks<Op>::value + 1) * S::TR * M * static_cast<int32_t>(sizeof(T));
-    const TileRange tr = tile_range(ntiles, P, plane_chunks(P, A.reach, S::TR, kBlockBytes));
+    const TileRange tr = tile_range(plan);
     constexpr int CO_PT = ((S::NZCAP + 8) / 8 + kBlock - 1) / kBlock;
     for (int32_t step = tr.first; step < tr.end; step += tr.stride) {
         const int32_t tile = tr.tile(step);
-        if (tile >= ntiles)
+        if (tile >= plan.ntiles)
             continue;
-        const int32_t r0 = tile * S::TR;
-        const int nr = min(S::TR, A.n - r0);
+        const int32_t r0 = tile * tr_rows;
+        const int nr = min(tr_rows, A.n - r0);
         for (int k = tid; k <= nr; k += kBlock)
             s_rp[k] = A.rp[r0 + k];
         __syncthreads();
@@ -693,7 +712,7 @@ __device__ __forceinline__ void gspmv_tiles_dict(const CsrView<T> &A, const Op &
         __syncthreads();
         const uint16_t *lco = s_code + lead;
 #pragma unroll 1
-        for (int p = 0; p < S::PASSES; ++p) {
+        for (int p = 0; p < plan.passes; ++p) {
             const int row_l = p * S::RPP + rl;
             if (lane_on && row_l < nr) {
                 const int32_t row = r0 + row_l;
@@ -730,9 +749,10 @@ __device__ __forceinline__ void gspmv_tiles_dict(const CsrView<T> &A, const Op &
 // column indices (the code array carries 4 codes of padding).
 template <typename T, int M, class Op>
 __device__ __forceinline__ void gspmv_tiles_cc(const CsrView<T> &A, const Op &op,
-                                               Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, int32_t *s_rp,
+                                               Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan, int32_t *s_rp,
                                                unsigned char *s_buf)
 {
+    const int tr_rows = plan.passes * Shape<T, M>::RPP;
     using S = Shape<T, M>;
     using LD = TileLds<T, M>;
     using I4 = int __attribute__((ext_vector_type(4)));
@@ -748,17 +768,14 @@ __device__ __forceinline__ void gspmv_tiles_cc(const CsrView<T> &A, const Op &op
     // (visible after the first tile's barrier)
     const int cb = A.cb;
     const uint32_t cmask = cb >= 32 ? 0xffffffffu : (1u << cb) - 1u;
-    const int32_t ntiles = static_cast<int32_t>((static_cast<int64_t>(A.n) + S::TR - 1) / S::TR);
-    const int32_t P = plane_tiles(A.reach, S::TR, ntiles);
-    constexpr int32_t kBlockBytes = (gathered_blocks<Op>::value + 1) * S::TR * M * static_cast<int32_t>(sizeof(T));
-    const TileRange tr = tile_range(ntiles, P, plane_chunks(P, A.reach, S::TR, kBlockBytes));
+    const TileRange tr = tile_range(plan);
     constexpr int CC_PT = ((S::NZCAP + 4) / 4 + kBlock - 1) / kBlock;
     for (int32_t step = tr.first; step < tr.end; step += tr.stride) {
         const int32_t tile = tr.tile(step);
-        if (tile >= ntiles)
+        if (tile >= plan.ntiles)
             continue;
-        const int32_t r0 = tile * S::TR;
-        const int nr = min(S::TR, A.n - r0);
+        const int32_t r0 = tile * tr_rows;
+        const int nr = min(tr_rows, A.n - r0);
         for (int k = tid; k <= nr; k += kBlock)
             s_rp[k] = A.rp[r0 + k];
         __syncthreads();
@@ -787,7 +804,7 @@ __device__ __forceinline__ void gspmv_tiles_cc(const CsrView<T> &A, const Op &op
         __syncthreads();
         const uint32_t *lcc = s_cc + lead;
 #pragma unroll 1
-        for (int p = 0; p < S::PASSES; ++p) {
+        for (int p = 0; p < plan.passes; ++p) {
             const int row_l = p * S::RPP + rl;
             if (lane_on && row_l < nr) {
                 const int32_t row = r0 + row_l;
@@ -819,17 +836,18 @@ __device__ __forceinline__ void gspmv_tiles_cc(const CsrView<T> &A, const Op &op
 
 template <typename T, int M, class Op>
 __device__ __forceinline__ void gspmv_tiles(const CsrView<T> &A, const Op &op,
-                                            Acc<T, Shape<T, M>::VW, Op::NDOT> &acc)
+                                            Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan)
 {
     using S = Shape<T, M>;
+    const int tr_rows = plan.passes * S::RPP;
     __shared__ int32_t s_rp[S::TR + 1];
     __shared__ __align__(16) unsigned char s_buf[TileLds<T, M>::BYTES];
     if (A.code) {
-        gspmv_tiles_dict<T, M>(A, op, acc, s_rp, s_buf);
+        gspmv_tiles_dict<T, M>(A, op, acc, plan, s_rp, s_buf);
         return;
     }
     if (A.ccode) {
-        gspmv_tiles_cc<T, M>(A, op, acc, s_rp, s_buf);
+        gspmv_tiles_cc<T, M>(A, op, acc, plan, s_rp, s_buf);
         return;
     }
     int32_t *s_ci = reinterpret_cast<int32_t *>(s_buf);
@@ -839,16 +857,13 @@ __device__ __forceinline__ void gspmv_tiles(const CsrView<T> &A, const Op &op,
     const int rl = S::row_of(tid);
     const typename Op::Lane ln = op.lane(g < S::G ? g : 0);
     const bool lane_on = S::used(tid) && g < S::G && ln.on;
-    const int32_t ntiles = static_cast<int32_t>((static_cast<int64_t>(A.n) + S::TR - 1) / S::TR);
-    const int32_t P = plane_tiles(A.reach, S::TR, ntiles);
-    constexpr int32_t kBlockBytes = (gathered_blocks<Op>::value + 1) * S::TR * M * static_cast<int32_t>(sizeof(T));
-    const TileRange tr = tile_range(ntiles, P, plane_chunks(P, A.reach, S::TR, kBlockBytes));
+    const TileRange tr = tile_range(plan);
     for (int32_t step = tr.first; step < tr.end; step += tr.stride) {
         const int32_t tile = tr.tile(step);
-        if (tile >= ntiles)  // past the end of the last, partial plane
+        if (tile >= plan.ntiles)  // past the end of the last, partial plane
             continue;
-        const int32_t r0 = tile * S::TR;
-        const int nr = min(S::TR, A.n - r0);
+        const int32_t r0 = tile * tr_rows;
+        const int nr = min(tr_rows, A.n - r0);
         for (int k = tid; k <= nr; k += kBlock)
             s_rp[k] = A.rp[r0 + k];
         __syncthreads();
@@ -901,7 +916,7 @@ __device__ __forceinline__ void gspmv_tiles(const CsrView<T> &A, const Op &op,
         const int32_t *lci = s_ci + lead;
         const T *lva = s_va + lead;
 #pragma unroll 1
-        for (int p = 0; p < S::PASSES; ++p) {
+        for (int p = 0; p < plan.passes; ++p) {
             const int row_l = p * S::RPP + rl;
             if (lane_on && row_l < nr) {
                 const int j0 = s_rp[row_l] - z0;
@@ -1194,16 +1209,20 @@ __device__ __forceinline__ void gspmv_march(const CsrView<T> &A, const Op &op,
     }
 }
 
-// Products over matrices with long rows (the Galerkin operators of coarse
-// multigrid levels carry 30-90 nonzeros per row): a wave takes one row at a
-// time, its RW row slots of L lanes take every RW-th entry of the row (NB at
-// a time, all gathers in flight together), a butterfly over the slots adds the
-// partial sums, and slot 0 runs the op's epilogue.  Workgroup b belongs to
-// XCD group b % 8, which owns a contiguous eighth of the rows.  Only for row
-// layouts whose lanes fill the wave (L a power of two).
+// Products over matrices of few rows, long ones among them (coarse multigrid
+// levels and their transfers).  What bounds them is the chain of dependent
+// loads (row offsets, entries, block rows), so nothing is staged and rows are
+// spread over all the waves there are: a row is taken by `slots` (a power of
+// two) of a wave's RW row slots of L lanes, which take every slots-th of its
+// entries (NB at a time, all gathers in flight together); a butterfly over the
+// row's slots adds the partial sums, and the first slot runs the op's
+// epilogue.  Workgroup b belongs to XCD group b % 8, which owns a contiguous
+// eighth of the rows.  Only for row layouts whose lanes fill the wave (L a
+// power of two).  Galerkin operator of 83,170 rows with 24 entries each: a
+// whole wave per row 70 us at m = 1 and 67 at m = 16, this 25 and 54 us.
 template <typename T, int M, class Op>
 __device__ __forceinline__ void gspmv_rows_split(const CsrView<T> &A, const Op &op,
-                                                 Acc<T, Shape<T, M>::VW, Op::NDOT> &acc)
+                                                 Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, int slots)
 {
     using S = Shape<T, M>;
     static_assert(S::POW2 && S::RW * S::L == 64, "row slots must fill the wave");
@@ -1211,33 +1230,37 @@ __device__ __forceinline__ void gspmv_rows_split(const CsrView<T> &A, const Op &
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int g = lane % S::L;
-    const int slot = lane / S::L;
+    const int slot = (lane / S::L) & (slots - 1);
+    const int rows_w = S::RW / slots;  // rows a wave takes together
     const typename Op::Lane ln = op.lane(g < S::G ? g : 0);
     const bool lane_on = g < S::G && ln.on;
     const int grp = blockIdx.x % kGroups;
     const int32_t q = blockIdx.x / kGroups, gx = gridDim.x / kGroups;
     const int32_t lo = static_cast<int32_t>(static_cast<int64_t>(A.n) * grp / kGroups);
     const int32_t hi = static_cast<int32_t>(static_cast<int64_t>(A.n) * (grp + 1) / kGroups);
-    const int32_t waves = kBlock / 64;
-    for (int32_t row = lo + q * waves + (tid >> 6); row < hi; row += gx * waves) {
-        const int32_t j0 = A.rp[row], j1 = A.rp[row + 1];
+    const int32_t step = gx * (kBlock / 64) * rows_w;
+    const int32_t sub = (tid >> 6) * rows_w + lane / (S::L * slots);
+    for (int32_t base = lo + q * (kBlock / 64) * rows_w; base < hi; base += step) {
+        const int32_t row = base + sub;
+        const bool on = lane_on && row < hi;
         T sum[S::VW];
 #pragma unroll
         for (int v = 0; v < S::VW; ++v)
             sum[v] = T(0);
         [[maybe_unused]] typename pre_of<Op>::type pr{};
-        if (lane_on) {
+        if (on) {
+            const int32_t j0 = A.rp[row], j1 = A.rp[row + 1];
             if constexpr (has_pre<Op>::value) {
                 if (slot == 0)
                     pr = op.pre(ln, row, g);
             }
-            for (int32_t jb = j0 + slot; jb < j1; jb += S::RW * NB) {
+            for (int32_t jb = j0 + slot; jb < j1; jb += slots * NB) {
                 int32_t c[NB];
                 T a[NB], x[NB][S::VW];
                 bool ok[NB];
 #pragma unroll
                 for (int k = 0; k < NB; ++k) {
-                    const int32_t j = jb + k * S::RW;
+                    const int32_t j = jb + k * slots;
                     ok[k] = j < j1;
                     const int32_t jj = ok[k] ? j : jb;
                     c[k] = A.ci[jj];
@@ -1254,12 +1277,11 @@ __device__ __forceinline__ void gspmv_rows_split(const CsrView<T> &A, const Op &
                             sum[v] += a[k] * x[k][v];
             }
         }
-#pragma unroll
-        for (int off = S::L; off < 64; off <<= 1)
+        for (int off = S::L; off < S::L * slots; off <<= 1)
 #pragma unroll
             for (int v = 0; v < S::VW; ++v)
                 sum[v] += __shfl_xor(sum[v], off);
-        if (lane_on && slot == 0) {
+        if (on && slot == 0) {
             if constexpr (has_pre<Op>::value)
                 op.row(ln, row, g, sum, acc, pr);
             else
@@ -1271,9 +1293,10 @@ __device__ __forceinline__ void gspmv_rows_split(const CsrView<T> &A, const Op &
 // Elementwise pass over every row of this workgroup's tiles.
 template <typename T, int M, class Op>
 __device__ __forceinline__ void stream_tiles(int32_t n, const Op &op,
-                                             Acc<T, Shape<T, M>::VW, Op::NDOT> &acc)
+                                             Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan)
 {
     using S = Shape<T, M>;
+    const int tr_rows = plan.passes * S::RPP;
     const int tid = threadIdx.x;
     const int g = S::lane_of(tid);
     const int rl = S::row_of(tid);
@@ -1282,13 +1305,12 @@ __device__ __forceinline__ void stream_tiles(int32_t n, const Op &op,
     const typename Op::Lane ln = op.lane(g);
     if (!ln.on)
         return;
-    const int32_t ntiles = static_cast<int32_t>((static_cast<int64_t>(n) + S::TR - 1) / S::TR);
-    const TileRange tr = tile_range(ntiles);
+    const TileRange tr = tile_range(plan);
     for (int32_t tile = tr.first; tile < tr.end; tile += tr.stride) {
-        const int32_t r0 = tile * S::TR;
-        const int nr = min(S::TR, n - r0);
+        const int32_t r0 = tile * tr_rows;
+        const int nr = min(tr_rows, n - r0);
 #pragma unroll 2
-        for (int p = 0; p < S::PASSES; ++p) {
+        for (int p = 0; p < plan.passes; ++p) {
             const int row_l = p * S::RPP + rl;
             if (row_l < nr)
                 op.row(ln, r0 + row_l, g, acc);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstddef>
 #include <cstdint>
@@ -65,6 +66,7 @@ void clear_error();
 // every CU at its occupancy limit, never more than there are tiles, rounded
 // up to a multiple of kGroups.
 int grid_for(const void *kernel, int64_t n, int tile_rows, int max_per_cu = 0);
+int num_cu();
 int max_grid();  // upper bound of grid_for over all kernels (for buffer sizing)
 
 template <typename T>
@@ -126,11 +128,11 @@ inline CsrView<float> user_view<float>(const mrhs_csr_s &A)
 void rcm_permutation(int32_t n, const int32_t *rp, const int32_t *ci, int32_t *perm);
 
 template <typename T, int M, class Op>
-__global__ void __launch_bounds__(kBlock) k_gspmv(CsrView<T> A, Op op, RedBufs<T> rb)
+__global__ void __launch_bounds__(kBlock) k_gspmv(CsrView<T> A, Op op, RedBufs<T> rb, TilePlan plan)
 {
     Acc<T, Shape<T, M>::VW, Op::NDOT> acc;
     acc.zero();
-    gspmv_tiles<T, M>(A, op, acc);
+    gspmv_tiles<T, M>(A, op, acc, plan);
     if constexpr (Op::NDOT > 0)
         grid_reduce<T, M, Op::NDOT>(acc, rb, op);
 }
@@ -159,21 +161,21 @@ int32_t march_runs(int32_t n, int32_t reach, int tile_rows, int grid);
 int march_mode();
 
 template <typename T, int M, class Op>
-__global__ void __launch_bounds__(kBlock) k_gspmv_split(CsrView<T> A, Op op, RedBufs<T> rb)
+__global__ void __launch_bounds__(kBlock) k_gspmv_split(CsrView<T> A, Op op, RedBufs<T> rb, int slots)
 {
     Acc<T, Shape<T, M>::VW, Op::NDOT> acc;
     acc.zero();
-    gspmv_rows_split<T, M>(A, op, acc);
+    gspmv_rows_split<T, M>(A, op, acc, slots);
     if constexpr (Op::NDOT > 0)
         grid_reduce<T, M, Op::NDOT>(acc, rb, op);
 }
 
 template <typename T, int M, class Op>
-__global__ void __launch_bounds__(kBlock) k_stream(int32_t n, Op op, RedBufs<T> rb)
+__global__ void __launch_bounds__(kBlock) k_stream(int32_t n, Op op, RedBufs<T> rb, TilePlan plan)
 {
     Acc<T, Shape<T, M>::VW, Op::NDOT> acc;
     acc.zero();
-    stream_tiles<T, M>(n, op, acc);
+    stream_tiles<T, M>(n, op, acc, plan);
     if constexpr (Op::NDOT > 0)
         grid_reduce<T, M, Op::NDOT>(acc, rb, op);
 }
@@ -187,15 +189,45 @@ extern int g_trace_every;
 int trace_begin(hipStream_t s, const char *name, int elem_bytes, int m, int grid, bool windows = false);
 void trace_end(int slot, hipStream_t s);
 
+// Passes per tile of a kernel over n rows: PASSES (256-row tiles).  Kernels
+// with a grid reduction take fewer where that would leave CUs without a tile
+// (a 32^3 operator has 128 tiles of 256 rows) and aim at one workgroup per CU,
+// since the reduction's last workgroups read every workgroup's sums: 32^3
+// Dirichlet, m = 16, spmv_sigma 18.1 us on 128 workgroups, 14.8 on 256, 16.5
+// on 512, 21.6 on 1024.  Without a reduction more workgroups do not pay: a
+// plain product on the same block takes 16.5 us on 128 and 19.0 on 256.
+template <typename T, int M, class Op>
+inline int tile_passes(int32_t n)
+{
+    using S = Shape<T, M>;
+    if constexpr (Op::NDOT == 0)
+        return S::PASSES;
+    const int64_t rows = static_cast<int64_t>(num_cu()) * S::RPP;
+    return static_cast<int>(std::min<int64_t>(S::PASSES, std::max<int64_t>(1, n / rows)));
+}
+
+// Row slots of a wave that share a row in gspmv_rows_split: as many as leave
+// each at most one gather batch of an average row (avg entries).  V-cycle of
+// the 524k-row channel with 0.6 / 1 / 1.5 times as many: m = 1 403 / 388 / 399
+// us, m = 16 785 / 801 / 843 us.
+inline int split_slots(int32_t avg, int row_slots)
+{
+    int slots = 1;
+    while (slots < row_slots && slots * MRHS_GATHER_BATCH < avg)
+        slots *= 2;
+    return slots;
+}
+
 template <typename T, int M, class Op>
 inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<T> &rb, hipStream_t s)
 {
     if constexpr (Shape<T, M>::POW2 && long_rows_ok<Op>::value) {
-        if (A.split) {  // long rows: one wave per row
+        if (A.split) {
             const void *fn = reinterpret_cast<const void *>(&k_gspmv_split<T, M, Op>);
-            const int grid = grid_for(fn, A.n, kBlock / 64);
+            const int slots = split_slots(A.split, Shape<T, M>::RW);
+            const int grid = grid_for(fn, A.n, kBlock / 64 * (Shape<T, M>::RW / slots));
             const int slot = g_trace_every ? trace_begin(s, Op::kName, static_cast<int>(sizeof(T)), M, grid) : -1;
-            hipLaunchKernelGGL((k_gspmv_split<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb);
+            hipLaunchKernelGGL((k_gspmv_split<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, slots);
             if (slot >= 0)
                 trace_end(slot, s);
             return hipGetLastError();
@@ -215,9 +247,12 @@ inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<
         }
     }
     const void *fn = reinterpret_cast<const void *>(&k_gspmv<T, M, Op>);
-    const int grid = grid_for(fn, A.n, Shape<T, M>::TR, max_per_cu<Op>::value);
+    const TilePlan plan =
+        tile_plan(A.n, tile_passes<T, M, Op>(A.n), Shape<T, M>::RPP, A.reach,
+                  (gathered_blocks<Op>::value + 1) * M * static_cast<int32_t>(sizeof(T)));
+    const int grid = grid_for(fn, A.n, Shape<T, M>::RPP * plan.passes, max_per_cu<Op>::value);
     const int slot = g_trace_every ? trace_begin(s, Op::kName, static_cast<int>(sizeof(T)), M, grid) : -1;
-    hipLaunchKernelGGL((k_gspmv<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb);
+    hipLaunchKernelGGL((k_gspmv<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
     if (slot >= 0)
         trace_end(slot, s);
     return hipGetLastError();
@@ -227,9 +262,10 @@ template <typename T, int M, class Op>
 inline hipError_t launch_stream(int32_t n, const Op &op, const RedBufs<T> &rb, hipStream_t s)
 {
     const void *fn = reinterpret_cast<const void *>(&k_stream<T, M, Op>);
-    const int grid = grid_for(fn, n, Shape<T, M>::TR, max_per_cu<Op>::value);
+    const TilePlan plan = tile_plan(n, tile_passes<T, M, Op>(n), Shape<T, M>::RPP);
+    const int grid = grid_for(fn, n, Shape<T, M>::RPP * plan.passes, max_per_cu<Op>::value);
     const int slot = g_trace_every ? trace_begin(s, Op::kName, static_cast<int>(sizeof(T)), M, grid) : -1;
-    hipLaunchKernelGGL((k_stream<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, n, op, rb);
+    hipLaunchKernelGGL((k_stream<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, n, op, rb, plan);
     if (slot >= 0)
         trace_end(slot, s);
     return hipGetLastError();

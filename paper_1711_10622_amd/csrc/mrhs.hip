@@ -38,7 +38,7 @@ std::mutex g_grid_mu;
 std::unordered_map<const void *, int> g_blocks_per_cu;
 int g_num_cu = 0;
 
-int num_cu()
+int num_cu_locked()
 {
     if (g_num_cu == 0) {
         int dev = 0, cu = 0;
@@ -56,8 +56,14 @@ int num_cu()
 int max_grid()
 {
     std::lock_guard<std::mutex> lk(g_grid_mu);
-    const int g = num_cu() * (2048 / kBlock);
+    const int g = num_cu_locked() * (2048 / kBlock);
     return (g + kGroups - 1) / kGroups * kGroups;
+}
+
+int num_cu()
+{
+    std::lock_guard<std::mutex> lk(g_grid_mu);
+    return num_cu_locked();
 }
 
 int grid_for(const void *kernel, int64_t n, int tile_rows, int max_per_cu)
@@ -65,7 +71,7 @@ int grid_for(const void *kernel, int64_t n, int tile_rows, int max_per_cu)
     int per_cu = 1, cus = 0;
     {
         std::lock_guard<std::mutex> lk(g_grid_mu);
-        cus = num_cu();
+        cus = num_cu_locked();
         auto it = g_blocks_per_cu.find(kernel);
         if (it == g_blocks_per_cu.end()) {
             int nb = 0;

@@ -83,6 +83,26 @@ def test_integer_exact_bitwise(torch_cuda, mrhs, m):
     assert np.array_equal(gpu_gspmv(mrhs, torch_cuda, A, X, dtype=np.float32), ref)
 
 
+@pytest.mark.parametrize("n", [31, 33, 8191, 65535, 65537, 131072 + 255, 262144 + 31])
+def test_tile_rows_follow_the_size(torch_cuda, mrhs, n):
+    """Tiles hold fewer rows where a matrix has too few to give every
+    workgroup a full one: sizes on both sides of where the passes per tile
+    change, with ragged last tiles.  Integer inputs, so products are exact."""
+    offs = np.array([-300, -1, 0, 1, 300])
+    cols = np.arange(n)[:, None] + offs[None, :]
+    ok = (cols >= 0) & (cols < n)
+    vals = np.broadcast_to(np.array([2.0, -1.0, 5.0, -3.0, 1.0]), cols.shape) + (np.arange(n) % 3)[:, None]
+    rp = np.concatenate([[0], np.cumsum(ok.sum(1))]).astype(np.int32)
+    A = grids.CSRMatrix(n, rp, cols[ok].astype(np.int32), np.ascontiguousarray(vals[ok]))
+    for m in (1, 4, 7, 8, 16):
+        X = rng.int_block(n, m, 900 + m, -50, 50)
+        ref = np.zeros((n, m))
+        for k in range(5):
+            ref[ok[:, k]] += vals[ok[:, k], k][:, None] * X[cols[ok[:, k], k]]
+        assert np.array_equal(gpu_gspmv(mrhs, torch_cuda, A, X), ref), m
+        assert np.array_equal(gpu_gspmv(mrhs, torch_cuda, A, X, dtype=np.float32), ref), m
+
+
 def test_block_equals_single_columns_bitwise(torch_cuda, mrhs):
     A = grids.channel7(24, 10, 9, beta=2.0)
     X = rng.rhs_block(A.n, 6, 400)
