@@ -121,7 +121,11 @@ const char *mrhs_version(void);
  * stream 2 or 4 bytes per entry instead of 4 + 8 (binary64) or 4 + 4
  * (binary32) and sum exactly the same values in the same order.  Building it
  * reads the derived arrays back and takes one pass over the entries per
- * array; the environment variable MRHS_CSR_DICT=0 turns it off.  See
+ * array; the environment variable MRHS_CSR_DICT=0 turns it off.  Where whole
+ * rows of 16-bit codes repeat (at most 4096 different ones, eight rows each on
+ * average, 16,384 rows and more), the products that gain from it read one
+ * 2-byte pattern number per row and a table of patterns instead
+ * (MRHS_CSR_PATTERN=0: none); results are the same bit for bit.  See
  * csr_stream_bytes.
  */
 mrhs_status csr_create(int32_t n, int64_t nnz, const int32_t *row_ptr,
@@ -149,9 +153,9 @@ mrhs_status csr_info(mrhs_csr A, int32_t *n, int64_t *nnz, size_t *device_bytes)
 
 /*
  * Bytes one tiled product streams from the matrix arrays (Section 2.3: the
- * matrix part of the GSpMV memory traffic): the row offsets plus, per entry,
- * a 2- or 4-byte code in the dictionary form or a 4-byte column index and a
- * value otherwise.  dtype MRHS_F64 or MRHS_F32; scaled != 0 for the solvers'
+ * matrix part of the GSpMV memory traffic), row patterns left aside: the row
+ * offsets plus, per entry, a 2- or 4-byte code in the dictionary form or a
+ * 4-byte column index and a value otherwise.  dtype MRHS_F64 or MRHS_F32; scaled != 0 for the solvers'
  * column-scaled matrix A D^-1, 0 for A.  gspmv of a handle made with
  * MRHS_CSR_REORDER reads the caller's arrays in plain form.  EINVAL: NULL
  * handle or output, unknown dtype.

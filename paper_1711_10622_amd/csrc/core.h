@@ -93,6 +93,7 @@ struct Shape {
     static __device__ __forceinline__ int lane_of(int tid) { return (tid & 63) % L; }
     static __device__ __forceinline__ int row_of(int tid) { return (tid >> 6) * RW + (tid & 63) / L; }
     static __device__ __forceinline__ bool used(int tid) { return (tid & 63) < RW * L; }
+    static constexpr int ROW_BYTES = M * static_cast<int>(sizeof(T));
 };
 
 // ---- 8/16-byte vector access ------------------------------------------------
@@ -221,15 +222,39 @@ struct VecU {
 #define MRHS_NT_STORE 1
 #endif
 
+// A row of a wave that works on consecutive rows: row u + slot, u the same in
+// every lane.  Its addresses are a scalar base plus a 32-bit lane offset that
+// does not change from row to row, so a block access costs no vector address
+// arithmetic.  Products are written for both kinds of row (int32_t and URow).
+struct URow {
+    int32_t u;
+    int slot;
+    __device__ __forceinline__ operator int32_t() const { return u + slot; }
+};
+
+template <typename T>
+__device__ __forceinline__ T *row_ptr(T *base, int32_t row, int32_t ld, int at)
+{
+    return base + static_cast<size_t>(row) * ld + at;
+}
+
+template <typename T>
+__device__ __forceinline__ T *row_ptr(T *base, URow row, int32_t ld, int at)
+{
+    using C = std::conditional_t<std::is_const<T>::value, const char, char>;
+    C *b = reinterpret_cast<C *>(base + static_cast<int64_t>(row.u) * ld);
+    return reinterpret_cast<T *>(b + static_cast<uint32_t>((row.slot * ld + at) * static_cast<int>(sizeof(T))));
+}
+
 // Lane g's VW elements of row `row` of an n x M block whose rows lie ld
 // elements apart (ld = M, or 2M for a half of an interleaved pair of blocks).
 // The last lane of a row whose width VW does not divide reads its TAIL
 // elements one by one (the rest of v is zero), so no access leaves the row.
-template <typename T, int M>
-__device__ __forceinline__ void ld(const T *base, int32_t row, int g, T *v, int32_t ld = M)
+template <typename T, int M, class Row>
+__device__ __forceinline__ void ld(const T *base, Row row, int g, T *v, int32_t ld = M)
 {
     using S = Shape<T, M>;
-    const T *p = base + static_cast<size_t>(row) * ld + g * S::VW;
+    const T *p = row_ptr(base, row, ld, g * S::VW);
     if constexpr (S::TAIL == S::VW) {
         Vec<T, S::VW>::load(p, v);
     } else if (g == S::G - 1) {
@@ -244,11 +269,11 @@ __device__ __forceinline__ void ld(const T *base, int32_t row, int g, T *v, int3
 // Stores lane g's elements of a row; block outputs use streaming
 // (nontemporal) stores: every block is far larger than the caches, and
 // keeping written lines out of L2 leaves it to the gathered block rows.
-template <typename T, int M>
-__device__ __forceinline__ void st(T *base, int32_t row, int g, const T *v, int32_t ld = M)
+template <typename T, int M, class Row>
+__device__ __forceinline__ void st(T *base, Row row, int g, const T *v, int32_t ld = M)
 {
     using S = Shape<T, M>;
-    T *p = base + static_cast<size_t>(row) * ld + g * S::VW;
+    T *p = row_ptr(base, row, ld, g * S::VW);
     if constexpr (S::TAIL == S::VW) {
 #if MRHS_NT_STORE
         Vec<T, S::VW>::store_nt(p, v);
@@ -264,8 +289,6 @@ __device__ __forceinline__ void st(T *base, int32_t row, int g, const T *v, int3
     }
 }
 
-
-// 32-byte lanes: two 16-byte accesses
 
 // ---- tile schedule ------------------------------------------------------------
 // Steps s = first, first + stride, ... < end of this workgroup; step s is
@@ -389,6 +412,50 @@ inline TilePlan tile_plan(int32_t n, int passes, int pass_rows, int32_t reach = 
 constexpr int kDictOffs = 32;    // at most this many distinct offsets
 constexpr int kDictVals = 2048;  // and this many distinct values per array
 
+// Row-pattern form.  On a structured grid whole rows repeat: row i is its
+// pattern's list of (offset, value) entries in storage order, column
+// i + offset, and a pattern is one of a few thousand at most (a wall-normal
+// cell layer and the way the row meets the periodic edges).  A product then
+// reads 2 bytes per row, and the pattern table stays in cache.  The entries
+// past a pattern's length name the row itself with value 0 and are never
+// added, so whole batches may be loaded.
+template <typename T>
+struct PatEntry;
+template <>
+struct __align__(16) PatEntry<double> {
+    double v;
+    int32_t off, pad;
+};
+template <>
+struct __align__(8) PatEntry<float> {
+    float v;
+    int32_t off;
+};
+// The same for the rows a seven-point stencil gives, whose entries are at most
+// kFar distant ones in two groups around (i - 1, i, i + 1): the distant
+// entries, the three near values, and in meta which are there (0 for a
+// pattern of another shape).
+constexpr int kFar = 4;
+template <typename T>
+struct __align__(16) PatStencil {
+    T fv[kFar], nv[3];
+    int32_t fo[kFar];
+    int32_t meta;
+    // meta: 1, distant entries before the near ones (3 bits), distant entries
+    // (3 bits), one bit per near entry
+    static constexpr int32_t pack(int before, int far, bool l, bool c, bool r)
+    {
+        return 1 | before << 1 | far << 4 | (l ? 1 << 8 : 0) | (c ? 1 << 9 : 0) | (r ? 1 << 10 : 0);
+    }
+};
+constexpr int32_t kWholeStencil = PatStencil<double>::pack(2, 4, true, true, true);
+constexpr int kPatBatch = 4;          // entries are read four at a time
+constexpr int kPatMax = 4096;         // at most this many patterns
+constexpr int kPatEntries = 1 << 15;  // and this many table entries
+constexpr int kPatRowsPer = 8;        // and this many rows per pattern on average
+constexpr int32_t kPatMinRows = 16384;  // sizes at which products change form
+constexpr int32_t kPatRows = 1 << 21;   // (pattern_pays)
+
 template <typename T>
 struct CsrView {
     const int32_t *__restrict__ rp;
@@ -405,6 +472,13 @@ struct CsrView {
     int32_t noffs = 0, nvals = 0;
     int32_t ob = 0;  // bits of the offset index in a code
     int32_t cb = 0;  // bits of the column in a column code
+    // row-pattern form (gspmv_tiles_pat; null pid: one of the forms above)
+    const uint16_t *__restrict__ pid = nullptr;   // [n] pattern of each row
+    const PatEntry<T> *__restrict__ pent = nullptr;  // [npat * pk] entries, pk per pattern
+    const int32_t *__restrict__ plen = nullptr;   // [npat] entries of each pattern
+    const PatStencil<T> *__restrict__ pst = nullptr;  // [npat]
+    int32_t pk = 0;    // room for whole batches of kPatBatch and MRHS_GATHER_BATCH
+    int32_t npat = 0;
 };
 
 // One row of the product: sum over the row's entries in storage order of
@@ -831,6 +905,332 @@ __device__ __forceinline__ void gspmv_tiles_cc(const CsrView<T> &A, const Op &op
             }
         }
         __syncthreads();
+    }
+}
+
+// Ops whose Pre repeats what they gather at their own row may set kPreOwn =
+// true and declare pre_own(lane, row, g, own) taking it from there.
+template <class Op, class = void>
+struct has_pre_own : std::false_type {};
+template <class Op>
+struct has_pre_own<Op, std::void_t<decltype(Op::kPreOwn)>> : std::integral_constant<bool, Op::kPreOwn> {};
+
+#define MRHS_CONST_AS __attribute__((address_space(4)))
+
+// One row of the product in the row-pattern form: the pattern's entries in
+// storage order, four at a time (a batch of seven
+// would take the registers of the other rows' path down an occupancy step).
+template <typename T, int VW, class Op>
+__device__ __forceinline__ void row_product_pat(const PatEntry<T> *__restrict__ ent, int len, int32_t row, int g,
+                                                const Op &op, const typename Op::Lane &ln, T *sum)
+{
+    constexpr int NB = kPatBatch;
+    for (int j = 0; j < len; j += NB) {
+        int32_t c[NB];
+        T a[NB], x[NB][VW];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            c[k] = row + ent[j + k].off;
+            a[k] = ent[j + k].v;
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            op.gather(ln, c[k], g, x[k]);
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+#pragma unroll
+            for (int v = 0; v < VW; ++v)
+                if (j + k < len)
+                    sum[v] += a[k] * x[k][v];
+    }
+}
+
+// One gather batch of a pattern, the same in every lane: loaded through the
+// scalar cache into scalar registers.
+template <typename T>
+struct PatBatch {
+    static constexpr int NB = MRHS_GATHER_BATCH;
+    int32_t off[NB];
+    T v[NB];
+    int32_t len;  // of the whole pattern
+    __device__ __forceinline__ void load(const CsrView<T> &A, int32_t pat, int j)
+    {
+        const auto *e = (const MRHS_CONST_AS PatEntry<T> *)(A.pent) + (static_cast<size_t>(pat) * A.pk + j);
+        len = ((const MRHS_CONST_AS int32_t *)(A.plen))[pat];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            off[k] = e[k].off;
+            v[k] = e[k].v;
+        }
+    }
+};
+
+// The tiled product over the row-pattern form.  Nothing is staged: a lane
+// reads its row's pattern number (one pass ahead), the pattern's entries and
+// the block rows; the waves of a workgroup never wait for one another.  Where
+// all rows of a wave have one pattern (all but the ends of a grid line) its
+// entries come through scalar loads, repeated only when the pattern changes,
+// and block rows lie at scalar addresses.  Rows, tiles and their order are
+// those of gspmv_tiles, so sums and partial dot products are too.
+// Bound by the block rows' latency and, on large matrices, by how often they
+// come from memory; what it saves against staged codes is the matrix's bytes
+// (2 per row for 18), the staging's two barriers and its LDS.  Measured beside
+// pattern_pays.
+template <typename T, int M, class Op>
+__device__ __forceinline__ void gspmv_tiles_pat(const CsrView<T> &A, const Op &op,
+                                                Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan)
+{
+    using S = Shape<T, M>;
+    constexpr int VW = S::VW, RW = S::RW, NB = MRHS_GATHER_BATCH;
+    const int passes = plan.passes;
+    const int tr_rows = passes * S::RPP;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = S::lane_of(lane);
+    const typename Op::Lane ln = op.lane(g < S::G ? g : 0);
+    if (!(S::used(lane) && g < S::G && ln.on))
+        return;
+    const int slot = lane / S::L;
+    const int32_t n = A.n;
+    const TileRange tr = tile_range(plan);
+    PatBatch<T> pat;
+    int32_t loaded = -1;  // the pattern whose first batch is in pat
+    for (int32_t step = tr.first; step < tr.end; step += tr.stride) {
+        const int32_t tile = tr.tile(step);
+        if (tile >= plan.ntiles)
+            continue;
+        const int32_t end = min(tile * tr_rows + tr_rows, n);
+        int32_t base = tile * tr_rows + wave * RW;
+        if (base >= end)
+            continue;
+        int32_t pid = A.pid[min(base + slot, n - 1)], pid_next = 0;
+#pragma unroll 1
+        for (int p = 0; p < passes && base < end; ++p, base += S::RPP) {
+            const int32_t p0 = __builtin_amdgcn_readfirstlane(pid);
+            const bool same = __builtin_amdgcn_ballot_w64(pid != p0) == 0;
+            const bool on = base + slot < end;
+            const URow row{base, slot};
+            pid_next = A.pid[min(base + S::RPP + slot, n - 1)];
+            T sum[VW];
+#pragma unroll
+            for (int v = 0; v < VW; ++v)
+                sum[v] = T(0);
+            [[maybe_unused]] typename pre_of<Op>::type pr{};
+            if constexpr (has_pre<Op>::value)
+                if (on)
+                    pr = op.pre(ln, row, g);
+            auto batch = [&](const PatBatch<T> &b, int j) {
+                T x[NB][VW];
+#pragma unroll
+                for (int k = 0; k < NB; ++k)
+                    op.gather(ln, URow{base + b.off[k], slot}, g, x[k]);
+                // all of them are on their way before any is tested for: a
+                // gather used under a condition alone would sink behind it
+#pragma unroll
+                for (int k = 0; k < NB; ++k)
+#pragma unroll
+                    for (int v = 0; v < VW; ++v)
+                        asm volatile("" : "+v"(x[k][v]));
+#pragma unroll
+                for (int k = 0; k < NB; ++k)
+                    if (j + k < b.len) {
+#pragma unroll
+                        for (int v = 0; v < VW; ++v)
+                            sum[v] += b.v[k] * x[k][v];
+                    }
+            };
+            if (same) {
+                if (p0 != loaded)
+                    pat.load(A, p0, 0);
+                loaded = p0;
+                if (on)
+                    batch(pat, 0);
+                for (int j = NB; j < pat.len; j += NB) {
+                    PatBatch<T> rest;
+                    rest.load(A, p0, j);
+                    if (on)
+                        batch(rest, j);
+                }
+            } else if (on) {
+                row_product_pat<T, VW>(A.pent + static_cast<size_t>(pid) * A.pk, A.plen[pid], base + slot, g, op, ln,
+                                       sum);
+            }
+            asm volatile("" : "+v"(pid_next));  // waited for before the store: later, a wait would be for the store too
+            if (on) {
+                if constexpr (has_pre<Op>::value)
+                    op.row(ln, row, g, sum, acc, pr);
+                else
+                    op.row(ln, row, g, sum, acc);
+            }
+            pid = pid_next;
+        }
+    }
+}
+
+// gspmv_tiles_pat for ops that gather two blocks per entry.
+//
+// Of a stencil row's block rows, the row itself and its two neighbours lie in
+// lines the wave has just asked for, and the vector cache stalls on a request
+// to a line that is still on its way (58 % of all cycles on the 12.6M-row
+// channel, m = 16, when every entry was gathered).  So a group's own rows are
+// loaded once, one pass ahead, with the two rows beside it, and the
+// neighbours' values move between lanes.  A group whose rows all have one
+// stencil pattern (PatStencil) takes its values and offsets through scalar
+// loads, kept until the pattern changes, and its four distant rows at scalar
+// addresses; other groups gather every entry.  Measured beside pattern_pays.
+// With one block gathered there is less to save than a grid line's ends cost
+// (gspmv m = 8 513 -> 522 us, m = 1 92 -> 118).
+template <typename T, int M, class Op>
+__device__ __forceinline__ void gspmv_near_pat(const CsrView<T> &A, const Op &op,
+                                               Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan)
+{
+    using S = Shape<T, M>;
+    constexpr int VW = S::VW, RW = S::RW;
+    const int tr_rows = plan.passes * S::RPP;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = S::lane_of(lane);
+    const typename Op::Lane ln = op.lane(g < S::G ? g : 0);
+    if (!(S::used(lane) && g < S::G && ln.on))
+        return;
+    const int slot = lane / S::L;
+    const int from_left = slot > 0 ? lane - S::L : lane;
+    const int from_right = slot < RW - 1 ? lane + S::L : lane;
+    const int32_t n = A.n;
+    const TileRange tr = tile_range(plan);
+    // the group's rows, and the row before it (first half of the wave) or after
+    // it; lanes past the last row repeat it and store nothing, so that every
+    // lane takes part in the moves between lanes
+    auto rows = [&](int32_t b, T *x) { op.gather(ln, min(b + slot, n - 1), g, x); };
+    auto beside = [&](int32_t b, T *x) { op.gather(ln, max(0, min(slot < RW / 2 ? b - 1 : b + RW, n - 1)), g, x); };
+    T fv[kFar], nv[3];
+    int32_t fo[kFar], meta = 0;
+    int32_t loaded = -1;  // the pattern held in these
+    for (int32_t step = tr.first; step < tr.end; step += tr.stride) {
+        const int32_t tile = tr.tile(step);
+        if (tile >= plan.ntiles)
+            continue;
+        const int32_t end = min(tile * tr_rows + tr_rows, n);
+        int32_t base = tile * tr_rows + wave * RW;
+        if (base >= end)
+            continue;
+        int32_t pid = A.pid[min(base + slot, n - 1)], pid_next = 0;
+        T own[VW], side[VW], own_next[VW] = {}, side_next[VW] = {};
+        rows(base, own);
+        beside(base, side);
+        // waited for here: a wait inside the loop would also wait for the
+        // store of the turn before
+#pragma unroll
+        for (int v = 0; v < VW; ++v)
+            asm volatile("" : "+v"(own[v]), "+v"(side[v]), "+v"(pid));
+#pragma unroll 1
+        for (int p = 0; p < plan.passes && base < end; ++p, base += S::RPP) {
+            const int32_t p0 = __builtin_amdgcn_readfirstlane(pid);
+            bool stencil = base + RW <= end && __builtin_amdgcn_ballot_w64(pid != p0) == 0;
+            T left[VW], right[VW];
+#pragma unroll
+            for (int v = 0; v < VW; ++v) {
+                left[v] = __shfl(own[v], from_left);
+                right[v] = __shfl(own[v], from_right);
+            }
+            if (p + 1 < plan.passes && base + S::RPP < end) {
+                pid_next = A.pid[min(base + S::RPP + slot, n - 1)];
+                rows(base + S::RPP, own_next);
+                beside(base + S::RPP, side_next);
+            }
+            const bool on = base + slot < end;
+            const URow row{base, slot};
+            T sum[VW];
+#pragma unroll
+            for (int v = 0; v < VW; ++v)
+                sum[v] = T(0);
+            [[maybe_unused]] typename pre_of<Op>::type pr{};
+            if (stencil && p0 != loaded) {
+                const auto *e = (const MRHS_CONST_AS PatStencil<T> *)(A.pst) + p0;
+#pragma unroll
+                for (int k = 0; k < kFar; ++k) {
+                    fo[k] = e->fo[k];
+                    fv[k] = e->fv[k];
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    nv[k] = e->nv[k];
+                meta = e->meta;
+                loaded = p0;
+            }
+            stencil = stencil && meta != 0;
+            if (on) {
+                if constexpr (has_pre_own<Op>::value)
+                    pr = op.pre_own(ln, row, g, own);
+                else if constexpr (has_pre<Op>::value)
+                    pr = op.pre(ln, row, g);
+            }
+            if (stencil) {
+                T x[kFar][VW];
+#pragma unroll
+                for (int k = 0; k < kFar; ++k)
+                    op.gather(ln, URow{base + fo[k], slot}, g, x[k]);
+                auto add = [&](T a, const T *y) {
+#pragma unroll
+                    for (int v = 0; v < VW; ++v)
+                        sum[v] += a * y[v];
+                };
+#pragma unroll
+                for (int v = 0; v < VW; ++v) {
+                    left[v] = slot == 0 ? side[v] : left[v];
+                    right[v] = slot == RW - 1 ? side[v] : right[v];
+                }
+                if (meta == kWholeStencil) {
+                    add(fv[0], x[0]);
+                    add(fv[1], x[1]);
+                    add(nv[0], left);
+                    add(nv[1], own);
+                    add(nv[2], right);
+                    add(fv[2], x[2]);
+                    add(fv[3], x[3]);
+                } else {
+                    const int before = meta >> 1 & 7, far = meta >> 4 & 7;
+#pragma unroll
+                    for (int k = 0; k < kFar; ++k)
+#pragma unroll
+                        for (int v = 0; v < VW; ++v)
+                            asm volatile("" : "+v"(x[k][v]));  // on their way before any is tested for
+#pragma unroll
+                    for (int k = 0; k < kFar; ++k)
+                        if (k < before)
+                            add(fv[k], x[k]);
+                    if (meta & 1 << 8)
+                        add(nv[0], left);
+                    if (meta & 1 << 9)
+                        add(nv[1], own);
+                    if (meta & 1 << 10)
+                        add(nv[2], right);
+#pragma unroll
+                    for (int k = 0; k < kFar; ++k)
+                        if (k >= before && k < far)
+                            add(fv[k], x[k]);
+                }
+            } else if (on) {
+                row_product_pat<T, VW>(A.pent + static_cast<size_t>(pid) * A.pk, A.plen[pid], base + slot, g, op, ln,
+                                       sum);
+            }
+            // waited for before the store, for the same reason
+#pragma unroll
+            for (int v = 0; v < VW; ++v)
+                asm volatile("" : "+v"(own_next[v]), "+v"(side_next[v]), "+v"(pid_next));
+            if (on) {
+                if constexpr (has_pre<Op>::value)
+                    op.row(ln, row, g, sum, acc, pr);
+                else
+                    op.row(ln, row, g, sum, acc);
+            }
+#pragma unroll
+            for (int v = 0; v < VW; ++v) {
+                own[v] = own_next[v];
+                side[v] = side_next[v];
+            }
+            pid = pid_next;
+        }
     }
 }
 

@@ -200,5 +200,174 @@ Codes<V> codes(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, con
     return out;
 }
 
+// The row-pattern form (CsrView::pid) of a matrix whose two value arrays
+// both have 16-bit codes c0 and c1: rows with equal code sequences share a
+// pattern, numbered by first appearance.  ok = false when there are more
+// than kPatMax patterns, more than one pattern per kPatRowsPer rows (the
+// table would rival the codes it replaces: 16 bytes per entry of a pattern
+// against 2 per entry of every row), or a table past kPatEntries entries.
+struct Patterns {
+    bool ok = false;
+    int32_t pk = 0;               // entries per pattern in the table (whole batches)
+    std::vector<uint16_t> id;     // [n]
+    std::vector<int32_t> rep;     // a row of each pattern
+    std::vector<int32_t> len;     // its entries
+};
+
+// Distinct rows of a range, in order of first appearance.
+class RowSet {
+  public:
+    RowSet(const int32_t *rp, const uint16_t *c0, const uint16_t *c1) : rp_(rp), c0_(c0), c1_(c1)
+    {
+        slot_.assign(4 * kPatMax, 0);
+    }
+    std::vector<int32_t> rows;
+    bool same(int32_t a, int32_t b) const
+    {
+        const size_t na = rp_[a + 1] - rp_[a], nb = rp_[b + 1] - rp_[b];
+        return na == nb && std::memcmp(c0_ + rp_[a], c0_ + rp_[b], 2 * na) == 0 &&
+               std::memcmp(c1_ + rp_[a], c1_ + rp_[b], 2 * na) == 0;
+    }
+    // index of row i's pattern, inserting it; -1 when that would be the
+    // (kPatMax + 1)-th
+    int32_t add(int32_t i)
+    {
+        uint64_t h = static_cast<uint64_t>(rp_[i + 1] - rp_[i]);
+        for (int32_t j = rp_[i]; j < rp_[i + 1]; ++j)
+            h = KeySet<uint64_t>::hash(h ^ (static_cast<uint64_t>(c0_[j]) << 32 | c1_[j]));
+        for (uint64_t k = h & (slot_.size() - 1);; k = (k + 1) & (slot_.size() - 1)) {
+            if (!slot_[k]) {
+                if (rows.size() >= static_cast<size_t>(kPatMax))
+                    return -1;
+                rows.push_back(i);
+                slot_[k] = static_cast<int32_t>(rows.size());
+                return slot_[k] - 1;
+            }
+            if (same(rows[slot_[k] - 1], i))
+                return slot_[k] - 1;
+        }
+    }
+
+  private:
+    const int32_t *rp_;
+    const uint16_t *c0_, *c1_;
+    std::vector<int32_t> slot_;
+};
+
+inline Patterns patterns(int32_t n, const int32_t *rp, const uint16_t *c0, const uint16_t *c1)
+{
+    Patterns out;
+    const int T = threads();
+    std::vector<RowSet> local(T, RowSet(rp, c0, c1));
+    std::vector<char> over(T, 0);
+    out.id.resize(static_cast<size_t>(n));
+    row_ranges(n, T, [&](int32_t lo, int32_t hi, int t) {
+        for (int32_t i = lo; i < hi; ++i) {  // most rows repeat the one before
+            if (i > lo && local[t].same(i - 1, i)) {
+                out.id[i] = out.id[i - 1];
+                continue;
+            }
+            const int32_t k = local[t].add(i);
+            if (k < 0) {
+                over[t] = 1;
+                return;
+            }
+            out.id[i] = static_cast<uint16_t>(k);
+        }
+    });
+    RowSet all(rp, c0, c1);
+    std::vector<std::vector<uint16_t>> map(T);
+    for (int t = 0; t < T; ++t) {
+        if (over[t])
+            return out;
+        for (int32_t r : local[t].rows) {
+            const int32_t k = all.add(r);
+            if (k < 0)
+                return out;
+            map[t].push_back(static_cast<uint16_t>(k));
+        }
+    }
+    int32_t longest = 0;
+    for (int32_t r : all.rows) {
+        out.len.push_back(rp[r + 1] - rp[r]);
+        longest = std::max(longest, out.len.back());
+    }
+    auto whole = [&](int32_t nb) { return std::max(1, (longest + nb - 1) / nb) * nb; };
+    out.pk = std::max(whole(kPatBatch), whole(MRHS_GATHER_BATCH));
+    const int64_t npat = static_cast<int64_t>(all.rows.size());
+    if (npat * kPatRowsPer > n || npat * out.pk > kPatEntries)
+        return out;
+    row_ranges(n, T, [&](int32_t lo, int32_t hi, int t) {
+        for (int32_t i = lo; i < hi; ++i)
+            out.id[i] = map[t][out.id[i]];
+    });
+    out.rep = all.rows;
+    out.ok = true;
+    return out;
+}
+
+// The table of one value array: each pattern's entries from its
+// representative row, padded with entries of the row itself and value 0.
+inline std::vector<PatEntry<double>> pattern_table(const Patterns &p, const int32_t *rp, const int32_t *ci,
+                                                   const double *hv)
+{
+    std::vector<PatEntry<double>> tab(p.rep.size() * static_cast<size_t>(p.pk), PatEntry<double>{0.0, 0, 0});
+    for (size_t k = 0; k < p.rep.size(); ++k)
+        for (int32_t j = 0; j < p.len[k]; ++j) {
+            PatEntry<double> &e = tab[k * p.pk + j];
+            e.v = hv[rp[p.rep[k]] + j];
+            e.off = ci[rp[p.rep[k]] + j] - p.rep[k];
+        }
+    return tab;
+}
+
+inline std::vector<PatEntry<float>> round_table(const std::vector<PatEntry<double>> &tab)
+{
+    std::vector<PatEntry<float>> out;
+    out.reserve(tab.size());
+    for (const PatEntry<double> &e : tab)
+        out.push_back(PatEntry<float>{static_cast<float>(e.v), e.off});
+    return out;
+}
+
+// The patterns of stencil shape (PatStencil): at most kFar distant entries,
+// the near ones (offsets -1, 0, 1, each at most once and in this order)
+// together among them.
+template <typename V>
+std::vector<PatStencil<V>> stencil_table(const Patterns &p, const std::vector<PatEntry<V>> &tab)
+{
+    std::vector<PatStencil<V>> out(p.rep.size());
+    std::memset(static_cast<void *>(out.data()), 0, sizeof(PatStencil<V>) * out.size());
+    for (size_t k = 0; k < p.rep.size(); ++k) {
+        PatStencil<V> s{};
+        int far = 0, before = -1, last = -2;
+        bool has[3] = {false, false, false}, ok = true, left = false;  // left: past the near entries
+        for (int32_t j = 0; j < p.len[k] && ok; ++j) {
+            const PatEntry<V> &e = tab[k * p.pk + j];
+            if (e.off >= -1 && e.off <= 1) {
+                ok = !left && e.off > last;
+                last = e.off;
+                if (before < 0)
+                    before = far;
+                has[e.off + 1] = true;
+                s.nv[e.off + 1] = e.v;
+            } else {
+                left = before >= 0;
+                ok = far < kFar;
+                if (ok) {
+                    s.fo[far] = e.off;
+                    s.fv[far] = e.v;
+                    ++far;
+                }
+            }
+        }
+        if (!ok)
+            continue;
+        s.meta = PatStencil<V>::pack(before < 0 ? far : before, far, has[0], has[1], has[2]);
+        out[k] = s;
+    }
+    return out;
+}
+
 } // namespace dict
 } // namespace mrhs

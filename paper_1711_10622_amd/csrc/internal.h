@@ -47,6 +47,13 @@ struct mrhs_csr_s {
     int32_t cbits[4] = {0, 0, 0, 0};
     void *vtab[4] = {nullptr, nullptr, nullptr, nullptr};
     int32_t nvals[4] = {0, 0, 0, 0};
+    // row-pattern form (CsrView::pid) of all four arrays, when the rows repeat
+    // often enough
+    uint16_t *pid = nullptr;
+    int32_t *plen = nullptr;
+    int32_t pk = 0;
+    void *pent[4] = {nullptr, nullptr, nullptr, nullptr};
+    void *pst[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
 namespace mrhs {
@@ -78,6 +85,13 @@ template <typename T>
 inline CsrView<T> view_of(const mrhs_csr_s &A, const T *va, int k)
 {
     CsrView<T> v{A.rp, A.ci, va, A.n, A.reach, 0};
+    if (A.pid) {
+        v.pid = A.pid;
+        v.pent = static_cast<const PatEntry<T> *>(A.pent[k]);
+        v.pst = static_cast<const PatStencil<T> *>(A.pst[k]);
+        v.plen = A.plen;
+        v.pk = A.pk;
+    }
     if (A.code[k]) {
         v.code = A.code[k];
         v.otab = A.otab;
@@ -133,6 +147,19 @@ __global__ void __launch_bounds__(kBlock) k_gspmv(CsrView<T> A, Op op, RedBufs<T
     Acc<T, Shape<T, M>::VW, Op::NDOT> acc;
     acc.zero();
     gspmv_tiles<T, M>(A, op, acc, plan);
+    if constexpr (Op::NDOT > 0)
+        grid_reduce<T, M, Op::NDOT>(acc, rb, op);
+}
+
+template <typename T, int M, class Op>
+__global__ void __launch_bounds__(kBlock) k_gspmv_pat(CsrView<T> A, Op op, RedBufs<T> rb, TilePlan plan)
+{
+    Acc<T, Shape<T, M>::VW, Op::NDOT> acc;
+    acc.zero();
+    if constexpr (gathered_blocks<Op>::value == 2)
+        gspmv_near_pat<T, M>(A, op, acc, plan);
+    else
+        gspmv_tiles_pat<T, M>(A, op, acc, plan);
     if constexpr (Op::NDOT > 0)
         grid_reduce<T, M, Op::NDOT>(acc, rb, op);
 }
@@ -218,6 +245,31 @@ inline int split_slots(int32_t avg, int row_slots)
     return slots;
 }
 
+// Whether a product over n rows reads the row patterns of a matrix that has
+// them (else its codes).  Measured as kernel time, codes -> patterns:
+//  * plain products (no reduction) of kPatMinRows to kPatRows rows, and of
+//    narrow rows above: 938k-row channel (131x77x93) m = 1 25.9 -> 23.6 us, m =
+//    4 35 -> 28, m = 7 53 -> 48, m = 8 47 -> 40, binary32 m = 16 47 -> 39;
+//    12.6M-row channel m = 1 139 -> 111, m = 2 181 -> 129.  Wider rows of
+//    larger matrices wait for block rows, not for the matrix, and gain nothing
+//    from waves that run further apart (m = 4 317 -> 306, m = 7 661 -> 725, m =
+//    8 525 -> 533); nor do small matrices, whose short grid lines leave few
+//    waves with one pattern (16^3, m = 16: 10.8 -> 13.0);
+//  * two blocks gathered per entry past kPatRows: spmv_omega on the 12.6M-row
+//    channel m = 4 500 -> 448 us, m = 8 928 -> 849, m = 16 1790 -> 1651; on the
+//    524k-row one it is no faster (m = 4 28.0 -> 29.7, m = 16 79.2 -> 81.4);
+//  * the others never: spmv_sigma on the 524k-row channel m = 4 20.5 -> 22.9,
+//    32^3 m = 16 11.0 -> 11.6, xr_sigma m = 4 51 -> 55.
+template <typename T, int M, class Op>
+inline bool pattern_pays(int32_t n)
+{
+    if (gathered_blocks<Op>::value == 2)
+        return n > kPatRows;
+    if (gathered_blocks<Op>::value != 1 || Op::NDOT > 0 || n < kPatMinRows)
+        return false;
+    return n <= kPatRows || Shape<T, M>::ROW_BYTES <= 16;
+}
+
 template <typename T, int M, class Op>
 inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<T> &rb, hipStream_t s)
 {
@@ -246,13 +298,26 @@ inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<
             return hipGetLastError();
         }
     }
-    const void *fn = reinterpret_cast<const void *>(&k_gspmv<T, M, Op>);
     const TilePlan plan =
         tile_plan(A.n, tile_passes<T, M, Op>(A.n), Shape<T, M>::RPP, A.reach,
                   (gathered_blocks<Op>::value + 1) * M * static_cast<int32_t>(sizeof(T)));
-    const int grid = grid_for(fn, A.n, Shape<T, M>::RPP * plan.passes, max_per_cu<Op>::value);
+    const bool pat = A.pid && pattern_pays<T, M, Op>(A.n);
+    // a product with a reduction runs on the staged kernel's grid in every
+    // form, so that partial dot products do not depend on the form.  Else row
+    // patterns, which need no LDS, fit up to eight workgroups on a CU; more
+    // than four send wide rows' tiles in flight out of an XCD's L2 (12.6M-row
+    // channel, m = 8: 533 -> 553 us)
+    const void *fn = pat && Op::NDOT == 0 ? reinterpret_cast<const void *>(&k_gspmv_pat<T, M, Op>)
+                                          : reinterpret_cast<const void *>(&k_gspmv<T, M, Op>);
+    const int most = max_per_cu<Op>::value                                   ? max_per_cu<Op>::value
+                     : pat && Op::NDOT == 0 && Shape<T, M>::ROW_BYTES >= 64 ? 4
+                                                                             : 0;
+    const int grid = grid_for(fn, A.n, Shape<T, M>::RPP * plan.passes, most);
     const int slot = g_trace_every ? trace_begin(s, Op::kName, static_cast<int>(sizeof(T)), M, grid) : -1;
-    hipLaunchKernelGGL((k_gspmv<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
+    if (pat)
+        hipLaunchKernelGGL((k_gspmv_pat<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
+    else
+        hipLaunchKernelGGL((k_gspmv<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
     if (slot >= 0)
         trace_end(slot, s);
     return hipGetLastError();

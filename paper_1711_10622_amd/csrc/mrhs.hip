@@ -244,11 +244,19 @@ void free_csr(mrhs_csr_s *A)
 {
     if (!A)
         return;
+    for (int k = 0; k < 2; ++k) {  // binary32 arrays may share the binary64 codes
+        if (A->code[k + 2] == A->code[k])
+            A->code[k + 2] = nullptr;
+        if (A->ccode[k + 2] == A->ccode[k])
+            A->ccode[k + 2] = nullptr;
+    }
     void *ptrs[] = {A->rp,   A->ci,   A->val, A->valh, A->val32, A->valh32, A->diag,
                     A->dinv, A->perm, A->urp, A->uci, A->uval, A->uval32, A->otab,
                     A->code[0], A->code[1], A->code[2], A->code[3],
                     A->ccode[0], A->ccode[1], A->ccode[2], A->ccode[3],
-                    A->vtab[0], A->vtab[1], A->vtab[2], A->vtab[3]};
+                    A->vtab[0], A->vtab[1], A->vtab[2], A->vtab[3],
+                    A->pid, A->plen, A->pent[0], A->pent[1], A->pent[2], A->pent[3],
+                    A->pst[0], A->pst[1], A->pst[2], A->pst[3]};
     for (void *p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -270,45 +278,67 @@ mrhs_status dev_alloc(T **p, size_t count, size_t &total)
 
 constexpr size_t kPad = 4;  // elements of padding after the nnz entries
 
-// ---- dictionary form (CsrView::code, CsrView::ccode) --------------------------
-// Uploads the codes and value table of value array k (host values hv) when
-// it has a dictionary form.
-template <typename V>
-mrhs_status dict_array(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, const V *hv,
-                       const dict::Offsets &offs, int k, size_t &total)
+// ---- dictionary and row-pattern forms (CsrView::code, ::ccode, ::pid) ----------
+template <typename E>
+mrhs_status upload_vec(E **dst, const std::vector<E> &v, size_t &total)
 {
-    dict::Codes<V> c = dict::codes<V>(A->n, A->nnz, rp, ci, hv, offs);
+    const mrhs_status st = dev_alloc(dst, v.size(), total);
+    if (st != MRHS_OK)
+        return st;
+    const hipError_t e = hipMemcpy(*dst, v.data(), sizeof(E) * v.size(), hipMemcpyHostToDevice);
+    return e == hipSuccess ? MRHS_OK
+                           : set_error(MRHS_EDEVICE, "dictionary upload failed: %s", hipGetErrorString(e));
+}
+
+// Uploads the codes and value table of value array k when it has them.
+template <typename V>
+mrhs_status dict_array(mrhs_csr_s *A, const dict::Codes<V> &c, int k, size_t &total)
+{
     if (!c.ok)
         return MRHS_OK;
     V *dtab = nullptr;
-    mrhs_status st;
-    if ((st = dev_alloc(&dtab, c.tab.size(), total)))
-        return st;
+    mrhs_status st = upload_vec(&dtab, c.tab, total);
     A->vtab[k] = dtab;
     A->nvals[k] = static_cast<int32_t>(c.tab.size());
-    hipError_t e = hipMemcpy(dtab, c.tab.data(), sizeof(V) * c.tab.size(), hipMemcpyHostToDevice);
-    if (offs.ok) {
-        if ((st = dev_alloc(&A->code[k], c.code.size(), total)))
-            return st;
-        if (e == hipSuccess)
-            e = hipMemcpy(A->code[k], c.code.data(), sizeof(uint16_t) * c.code.size(), hipMemcpyHostToDevice);
-    } else {
-        if ((st = dev_alloc(&A->ccode[k], c.ccode.size(), total)))
-            return st;
-        A->cbits[k] = c.cb;
-        if (e == hipSuccess)
-            e = hipMemcpy(A->ccode[k], c.ccode.data(), sizeof(uint32_t) * c.ccode.size(), hipMemcpyHostToDevice);
-    }
-    if (e != hipSuccess)
-        return set_error(MRHS_EDEVICE, "dictionary upload failed: %s", hipGetErrorString(e));
-    return MRHS_OK;
+    if (st != MRHS_OK)
+        return st;
+    A->cbits[k] = c.cb;
+    return c.code.empty() ? upload_vec(&A->ccode[k], c.ccode, total) : upload_vec(&A->code[k], c.code, total);
+}
+
+// The pattern tables of binary64 value array k, and their roundings (to
+// nearest even) for the binary32 array k + 2.
+mrhs_status pattern_arrays(mrhs_csr_s *A, const dict::Patterns &p, const std::vector<PatEntry<double>> &tab, int k,
+                           size_t &total)
+{
+    PatEntry<double> *e = nullptr;
+    PatEntry<float> *e32 = nullptr;
+    PatStencil<double> *s = nullptr;
+    PatStencil<float> *s32 = nullptr;
+    const std::vector<PatEntry<float>> tab32 = dict::round_table(tab);
+    mrhs_status st = upload_vec(&e, tab, total);
+    if (st == MRHS_OK)
+        st = upload_vec(&e32, tab32, total);
+    if (st == MRHS_OK)
+        st = upload_vec(&s, dict::stencil_table(p, tab), total);
+    if (st == MRHS_OK)
+        st = upload_vec(&s32, dict::stencil_table(p, tab32), total);
+    A->pent[k] = e;
+    A->pent[k + 2] = e32;
+    A->pst[k] = s;
+    A->pst[k + 2] = s32;
+    return st;
 }
 
 // Builds the dictionary form of the solver arrays (rp, ci: the solver's
 // numbering, sval: its binary64 values on the host; the derived arrays are
 // read back from the device, so the tables hold exactly the values the
 // products use): 16-bit codes when the matrix has at most kDictOffs distinct
-// column offsets, else 32-bit column codes.  MRHS_CSR_DICT=0 turns it off.
+// column offsets, else 32-bit column codes.  Where the coded rows repeat
+// (dict::patterns) there is the row-pattern form too; the binary32
+// arrays are roundings of the binary64 ones, so rows equal in those are equal
+// in these.  MRHS_CSR_DICT=0 turns all forms off, MRHS_CSR_PATTERN=0 the
+// row-pattern form.
 mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, const double *sval, size_t &total)
 {
     if (!env_int("MRHS_CSR_DICT", 1, 0, 1) || A->nnz == 0)
@@ -317,32 +347,53 @@ mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, cons
     dict::offsets(A->n, rp, ci, offs);
     mrhs_status st;
     hipError_t e;
+    const size_t nnz = static_cast<size_t>(A->nnz);
+    std::vector<double> h(nnz);
+    if ((e = hipMemcpy(h.data(), A->valh, sizeof(double) * nnz, hipMemcpyDeviceToHost)))
+        return set_error(MRHS_EDEVICE, "read-back failed: %s", hipGetErrorString(e));
+    const dict::Codes<double> c0 = dict::codes<double>(A->n, A->nnz, rp, ci, sval, offs);
+    const dict::Codes<double> c1 = dict::codes<double>(A->n, A->nnz, rp, ci, h.data(), offs);
+    if (offs.ok && c0.ok && c1.ok && A->n >= kPatMinRows && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
+        const dict::Patterns p = dict::patterns(A->n, rp, c0.code.data(), c1.code.data());
+        if (p.ok) {
+            if ((st = upload_vec(&A->plen, p.len, total)) ||
+                (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, sval), 0, total)) ||
+                (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, h.data()), 1, total)))
+                return st;
+            A->pk = p.pk;
+            if ((st = upload_vec(&A->pid, p.id, total)))
+                return st;
+        }
+    }
     if (offs.ok) {
         A->noffs = static_cast<int32_t>(offs.set.keys.size());
         A->ob = offs.ob;
-        std::vector<int32_t> otab(offs.set.keys.begin(), offs.set.keys.end());
-        if ((st = dev_alloc(&A->otab, otab.size(), total)))
+        if ((st = upload_vec(&A->otab, std::vector<int32_t>(offs.set.keys.begin(), offs.set.keys.end()), total)))
             return st;
-        if ((e = hipMemcpy(A->otab, otab.data(), sizeof(int32_t) * otab.size(), hipMemcpyHostToDevice)))
-            return set_error(MRHS_EDEVICE, "dictionary upload failed: %s", hipGetErrorString(e));
     }
-    const dict::Offsets &po = offs;
-    const size_t nnz = static_cast<size_t>(A->nnz);
-    if ((st = dict_array<double>(A, rp, ci, sval, po, 0, total)))
+    if ((st = dict_array<double>(A, c0, 0, total)) || (st = dict_array<double>(A, c1, 1, total)))
         return st;
-    {
-        std::vector<double> h(nnz);
-        if ((e = hipMemcpy(h.data(), A->valh, sizeof(double) * nnz, hipMemcpyDeviceToHost)))
-            return set_error(MRHS_EDEVICE, "read-back failed: %s", hipGetErrorString(e));
-        if ((st = dict_array<double>(A, rp, ci, h.data(), po, 1, total)))
-            return st;
-    }
-    std::vector<float> h(nnz);
+    // the binary32 arrays: the binary64 codes with a rounded value table (equal
+    // values round alike), else codes of their own
     const float *src[2] = {A->val32, A->valh32};
     for (int k = 0; k < 2; ++k) {
-        if ((e = hipMemcpy(h.data(), src[k], sizeof(float) * nnz, hipMemcpyDeviceToHost)))
+        const dict::Codes<double> &c = k ? c1 : c0;
+        if (c.ok) {
+            float *tab = nullptr;
+            st = upload_vec(&tab, std::vector<float>(c.tab.begin(), c.tab.end()), total);
+            A->vtab[k + 2] = tab;
+            if (st != MRHS_OK)
+                return st;
+            A->nvals[k + 2] = A->nvals[k];
+            A->cbits[k + 2] = A->cbits[k];
+            A->code[k + 2] = A->code[k];
+            A->ccode[k + 2] = A->ccode[k];
+            continue;
+        }
+        std::vector<float> h32(nnz);
+        if ((e = hipMemcpy(h32.data(), src[k], sizeof(float) * nnz, hipMemcpyDeviceToHost)))
             return set_error(MRHS_EDEVICE, "read-back failed: %s", hipGetErrorString(e));
-        if ((st = dict_array<float>(A, rp, ci, h.data(), po, 2 + k, total)))
+        if ((st = dict_array<float>(A, dict::codes<float>(A->n, A->nnz, rp, ci, h32.data(), offs), 2 + k, total)))
             return st;
     }
     return MRHS_OK;

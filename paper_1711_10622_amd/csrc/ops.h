@@ -183,11 +183,13 @@ struct OpStore {
         bool on;
     };
     __device__ Lane lane(int) const { return {true}; }
-    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const
+    template <class Row>
+    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const
     {
         ld<T, M>(X, c, g, x);
     }
-    __device__ __forceinline__ void row(const Lane &, int32_t i, int g, const T *sum,
+    template <class Row>
+    __device__ __forceinline__ void row(const Lane &, Row i, int g, const T *sum,
                                         Acc<T, S::VW, NDOT> &) const
     {
         st<T, M>(Y, i, g, sum);
@@ -259,7 +261,8 @@ struct OpResid {
         }
         return ln;
     }
-    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, double *x) const
+    template <class Row>
+    __device__ __forceinline__ void gather(const Lane &, Row c, int g, double *x) const
     {
         ld<double, M>(X, c, g, x);
     }
@@ -267,13 +270,15 @@ struct OpResid {
     struct Pre {
         double b[S::VW];
     };
-    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
+    template <class Row>
+    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
     {
         Pre pr;
         ld<double, M>(B, i, g, pr.b);
         return pr;
     }
-    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const double *sum,
+    template <class Row>
+    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const double *sum,
                                         Acc<double, S::VW, NDOT> &acc, const Pre &pr) const
     {
         const size_t o = static_cast<size_t>(i) * M + g * S::VW;
@@ -471,11 +476,13 @@ struct OpSpmv1 {
     int32_t ldp;  // row stride of v
     using Lane = RunLane<T, M>;
     __device__ Lane lane(int g) const { return run_lane<T, M>(ctl, g); }
-    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const
+    template <class Row>
+    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const
     {
         ld<T, M>(p, c, g, x);
     }
-    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const T *sum,
+    template <class Row>
+    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const T *sum,
                                         Acc<T, S::VW, NDOT> &acc) const
     {
         T h[S::VW];
@@ -530,7 +537,8 @@ struct OpSpmv2 {
         }
         return ln;
     }
-    __device__ __forceinline__ void gather(const Lane &ln, int32_t c, int g, T *x) const
+    template <class Row>
+    __device__ __forceinline__ void gather(const Lane &ln, Row c, int g, T *x) const
     {
         T rr[S::VW], vv[S::VW];
         ld<T, M>(r, c, g, rr, ldp);
@@ -543,13 +551,25 @@ struct OpSpmv2 {
     struct Pre {
         T s[S::VW];
     };
-    __device__ __forceinline__ Pre pre(const Lane &ln, int32_t i, int g) const
+    template <class Row>
+    __device__ __forceinline__ Pre pre(const Lane &ln, Row i, int g) const
     {
         Pre pr;
         gather(ln, i, g, pr.s);
         return pr;
     }
-    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const T *sum,
+    static constexpr bool kPreOwn = true;
+    template <class Row>
+    __device__ __forceinline__ Pre pre_own(const Lane &, Row, int, const T *own) const
+    {
+        Pre pr;
+#pragma unroll
+        for (int q = 0; q < S::VW; ++q)
+            pr.s[q] = own[q];
+        return pr;
+    }
+    template <class Row>
+    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const T *sum,
                                         Acc<T, S::VW, NDOT> &acc, const Pre &pr) const
     {
         const T *s = pr.s;
@@ -782,7 +802,8 @@ struct OpXRSigma {
             pn = p;
         }
     }
-    __device__ __forceinline__ void gather(const Lane &ln, int32_t c, int g, T *x) const
+    template <class Row>
+    __device__ __forceinline__ void gather(const Lane &ln, Row c, int g, T *x) const
     {
         T rr[S::VW], vv[S::VW], tt[S::VW], pp[S::VW];
         ld<T, M>(r, c, g, rr, ldp);
@@ -798,7 +819,8 @@ struct OpXRSigma {
     struct Pre {
         T y[S::VW], r[S::VW], v[S::VW], t[S::VW], p[S::VW];
     };
-    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
+    template <class Row>
+    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
     {
         Pre pr;
         ld<T, M>(y, i, g, pr.y);
@@ -808,7 +830,8 @@ struct OpXRSigma {
         ld<T, M>(p, i, g, pr.p);
         return pr;
     }
-    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const T *sum, Acc<T, S::VW, NDOT> &acc,
+    template <class Row>
+    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const T *sum, Acc<T, S::VW, NDOT> &acc,
                                         const Pre &pr) const
     {
         T yy[S::VW], rn[S::VW], pn[S::VW], hh[S::VW];
@@ -1163,15 +1186,17 @@ struct OpColsStore {
         bool on;
     };
     __device__ Lane lane(int) const { return {true}; }
-    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, double *x) const
+    template <class Row>
+    __device__ __forceinline__ void gather(const Lane &, Row c, int g, double *x) const
     {
 #pragma unroll
         for (int v = 0; v < S::VW; ++v) {
             const int q = g * S::VW + v;
-            x[v] = q < K ? z[q][c] : 0.0;
+            x[v] = q < K ? *row_ptr(z[q], c, 1, 0) : 0.0;
         }
     }
-    __device__ __forceinline__ void row(const Lane &, int32_t i, int g, const double *sum,
+    template <class Row>
+    __device__ __forceinline__ void row(const Lane &, Row i, int g, const double *sum,
                                         Acc<double, S::VW, NDOT> &) const
     {
 #pragma unroll
