@@ -207,6 +207,25 @@ __global__ void __launch_bounds__(kBlock) k_stream(int32_t n, Op op, RedBufs<T> 
         grid_reduce<T, M, Op::NDOT>(acc, rb, op);
 }
 
+// Streams of several columns' refinement vectors at once.  The columns'
+// reductions are separate (partial sums, groups' sums and tickets of each lie
+// after the column's before), each on the grid it would have alone, so a
+// column's arithmetic does not depend on which others are in the launch.
+// Memory bound (up to kGcrMax stored directions per column are read once).
+template <class Op>
+__global__ void __launch_bounds__(kBlock) k_cols(ColBatch cb, RedBufs<double> rb, TilePlan plan)
+{
+    const int y = blockIdx.y;
+    const Op op = cb.op<Op>(y);
+    const RedBufs<double> mine{rb.part + static_cast<size_t>(y) * gridDim.x * Op::NDOT,
+                               rb.gpart + y * kGroups * Op::NDOT,
+                               rb.tickets + y * kTicketStride * (kGroups + 1)};
+    Acc<double, 1, Op::NDOT> acc;
+    acc.zero();
+    stream_tiles<double, 1>(cb.n, op, acc, plan);
+    grid_reduce<double, 1, Op::NDOT>(acc, mine, op);
+}
+
 // ---- optional per-launch timing (mrhs_trace_enable) ---------------------
 // When enabled with period k, every k-th launch of each kernel class is
 // bracketed by a pair of HIP events on its own stream; mrhs_trace_read
@@ -336,6 +355,19 @@ inline hipError_t launch_stream(int32_t n, const Op &op, const RedBufs<T> &rb, h
     return hipGetLastError();
 }
 
+template <class Op>
+inline hipError_t launch_cols(const ColBatch &cb, int count, const RedBufs<double> &rb, hipStream_t s)
+{
+    const void *fn = reinterpret_cast<const void *>(&k_cols<Op>);
+    const TilePlan plan = tile_plan(cb.n, Shape<double, 1>::PASSES, Shape<double, 1>::RPP);
+    const int grid = grid_for(fn, cb.n, Shape<double, 1>::RPP * plan.passes);
+    const int slot = g_trace_every ? trace_begin(s, Op::kName, static_cast<int>(sizeof(double)), 1, grid) : -1;
+    hipLaunchKernelGGL((k_cols<Op>), dim3(grid, count), dim3(kBlock), 0, s, cb, rb, plan);
+    if (slot >= 0)
+        trace_end(slot, s);
+    return hipGetLastError();
+}
+
 // Calls f.template operator()<M>() for the runtime value m in [1, 16].
 template <class F>
 inline auto dispatch_m(int m, F &&f)
@@ -410,6 +442,7 @@ struct Ctx {
     Kry<float> *kry32;
     RedBufs<double> rb64;
     RedBufs<float> rb32;
+    RedBufs<double> rbcol;  // of k_cols: tickets for kColBatch columns
     double *r, *p, *v, *t;
     double *r64;
     GcrBlocks gcr;
@@ -472,6 +505,7 @@ class Engine {
     const AmgStepTable *AT_ = nullptr;
     Ctx c_{};
     unsigned *tickets_ = nullptr;
+    unsigned *col_tickets_ = nullptr;  // kColBatch sets (mixed precision)
     Ctl *host_ = nullptr;
     bool own_host_ = false;
     int chunk_ = 16, ndirs_ = kGcrMax, max_outer_ = 500;

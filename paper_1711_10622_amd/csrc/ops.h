@@ -1356,6 +1356,51 @@ struct OpColUpdate {
     }
 };
 
+// The refinement ops of several columns, one launch for all: workgroups
+// (., y) stream column cols[y], whose vectors lie at offset cols[y] * n.
+constexpr int kColBatch = 8;  // columns per launch
+
+struct ColBatch {
+    GcrBlocks gcr;
+    double *r;
+    Ctl *ctl;
+    int32_t n;
+    int32_t cols[kColBatch], jmax[kColBatch], slot[kColBatch];
+    template <class Op>
+    __device__ __forceinline__ Op op(int y) const
+    {
+        const int col = cols[y];
+        const size_t off = static_cast<size_t>(col) * n;
+        double *z = gcr.znew + off, *w = gcr.wnew + off;
+        Op o{};
+        o.col = col;
+        o.ctl = ctl;
+        if constexpr (std::is_same<Op, OpColUpdate>::value) {
+            o.xacc = gcr.xacc + off;
+            o.r = r + off;
+            o.z = z;
+            o.w = w;
+            o.zslot = gcr.z[slot[y]] + off;
+            o.wslot = gcr.w[slot[y]] + off;
+            o.ndirs = gcr.ndirs;
+        } else {
+            o.w = w;
+            o.jmax = jmax[y];
+#pragma unroll
+            for (int j = 0; j < kGcrMax; ++j) {
+                o.W[j] = gcr.w[j] + off;  // read only for j < jmax <= ndirs
+                if constexpr (std::is_same<Op, OpColOrth>::value)
+                    o.Z[j] = gcr.z[j] + off;
+            }
+            if constexpr (std::is_same<Op, OpColOrth>::value) {
+                o.z = z;
+                o.r = r + off;
+            }
+        }
+        return o;
+    }
+};
+
 // X(:, c) += x_acc(:, c) and x_acc(:, c) = 0 (FOLD), or x_acc(:, c) = 0
 // (ZERO), for the columns in cmask.
 enum FoldKind : int32_t { FOLD_ADD = 0, FOLD_ZERO = 1 };

@@ -116,8 +116,10 @@ Layout layout(int32_t n, int32_t m, uint32_t flags, const AmgDev *amg = nullptr)
     L.ctl = take(sizeof(Ctl));
     L.kry64 = take(sizeof(Kry<double>));
     L.kry32 = take(sizeof(Kry<float>));
-    // the partial sums have room for kMaxDots dots of kMaxM columns, more than
-    // any reduction has; the ticket counters' lines are taken out of it
+    // the partial sums have room for kMaxDots dots of kMaxM columns, twice what
+    // any reduction has (four dots of kMaxM columns; kMaxDots of each of
+    // kColBatch columns); the ticket counters' lines are taken out of it, those
+    // of k_cols lie at the start of its second half
     const size_t V = static_cast<size_t>(kMaxDots) * kMaxM;
     static_assert(sizeof(unsigned) * kTicketStride % kAlign == 0, "a counter fills whole lines");
     L.tickets = take(sizeof(unsigned) * kTicketStride * (kGroups + 1));
@@ -343,31 +345,33 @@ struct Steps {
             if (cp.k > 0)
                 MRHS_TRY(dispatch_m(cp.k, cp));
         }
-        for (int col = 0; col < M; ++col) {
-            if (!((cmask >> col) & 1u))
-                continue;
-            const size_t off = static_cast<size_t>(col) * n;
-            double *z = c.gcr.znew + off, *w = c.gcr.wnew + off, *r = c.r64 + off;
-            OpColDots dots{};
-            OpColOrth orth{};
-            for (int j = 0; j < kGcrMax; ++j) {
-                const bool have = j < c.gcr.ndirs;
-                dots.W[j] = orth.W[j] = have ? c.gcr.w[j] + off : nullptr;
-                orth.Z[j] = have ? c.gcr.z[j] + off : nullptr;
+        // the columns' steps, kColBatch to a launch: one column streams 2 MB
+        // vectors at 262,144 rows, which a launch of 13-20 us leaves mostly to
+        // its latency and reduction.  8 columns there: 24 launches to 3, a
+        // whole solve 26.8 -> 23.9 ms
+        ColBatch cb{c.gcr, c.r64, c.ctl, c.n, {}, {}, {}};
+        for (int next = 0; next < M;) {
+            int k = 0;
+            for (; next < M && k < kColBatch; ++next) {
+                if (!((cmask >> next) & 1u))
+                    continue;
+                cb.cols[k] = next;
+                cb.jmax[k] = jmax[next];
+                cb.slot[k++] = slot[next];
             }
-            dots.w = w;
-            dots.jmax = orth.jmax = jmax[col];
-            dots.col = orth.col = col;
-            dots.ctl = orth.ctl = c.ctl;
-            orth.w = w;
-            orth.z = z;
-            orth.r = r;
-            if (jmax[col] > 0)
-                MRHS_TRY((launch_stream<double, 1>(c.n, dots, c.rb64, c.s)));
-            MRHS_TRY((launch_stream<double, 1>(c.n, orth, c.rb64, c.s)));
-            const OpColUpdate upd{c.gcr.xacc + off, r, z, w, c.gcr.z[slot[col]] + off, c.gcr.w[slot[col]] + off,
-                                  c.gcr.ndirs, col, c.ctl};
-            MRHS_TRY((launch_stream<double, 1>(c.n, upd, c.rb64, c.s)));
+            if (k == 0)
+                break;
+            ColBatch dots = cb;  // those with stored directions to project on
+            int kd = 0;
+            for (int q = 0; q < k; ++q)
+                if (cb.jmax[q] > 0) {
+                    dots.cols[kd] = cb.cols[q];
+                    dots.jmax[kd++] = cb.jmax[q];
+                }
+            if (kd > 0)
+                MRHS_TRY((launch_cols<OpColDots>(dots, kd, c.rbcol, c.s)));
+            MRHS_TRY((launch_cols<OpColOrth>(cb, k, c.rbcol, c.s)));
+            MRHS_TRY((launch_cols<OpColUpdate>(cb, k, c.rbcol, c.s)));
         }
         return hipSuccess;
     }
@@ -459,6 +463,11 @@ Engine::Engine(const mrhs_csr_s &A, int m, uint32_t flags, void *ws, const doubl
     tickets_ = reinterpret_cast<unsigned *>(base + L.tickets);
     c_.rb64 = {reinterpret_cast<double *>(base + L.part), reinterpret_cast<double *>(base + L.gpart), tickets_};
     c_.rb32 = {reinterpret_cast<float *>(base + L.part), reinterpret_cast<float *>(base + L.gpart), tickets_};
+    const size_t half = static_cast<size_t>(kMaxDots) * kMaxM / 2 * static_cast<size_t>(max_grid());
+    static_assert(kMaxDots * kColBatch <= kMaxDots * kMaxM / 2, "partial sums of k_cols fit the first half");
+    static_assert(kMaxDots * kColBatch <= kMaxDots * kMaxM, "and the groups' sums their room");
+    col_tickets_ = reinterpret_cast<unsigned *>(c_.rb64.part + half);
+    c_.rbcol = {c_.rb64.part, c_.rb64.gpart, col_tickets_};
     ndirs_ = gcr_dirs();
     if (mixed_) {
         c_.r64 = reinterpret_cast<double *>(base + L.r64);
@@ -532,6 +541,9 @@ mrhs_status Engine::reset()
     waited_ = 0;
     constexpr int kTickets = kTicketStride * (kGroups + 1);
     hipLaunchKernelGGL(k_fill_u32, dim3((kTickets + 255) / 256), dim3(256), 0, s_, tickets_, kTickets, 0u);
+    if (mixed_)
+        hipLaunchKernelGGL(k_fill_u32, dim3((kTickets * kColBatch + 255) / 256), dim3(256), 0, s_, col_tickets_,
+                           kTickets * kColBatch, 0u);
     hipLaunchKernelGGL(k_ctl_reset, dim3(1), dim3(64), 0, s_, c_.ctl, mixed_ ? MODE_INNER : MODE_F64, tol_in_,
                        max_outer_, A_.n, stag_window_);
     MRHS_HIP(hipGetLastError());
