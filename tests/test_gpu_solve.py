@@ -98,6 +98,25 @@ def test_channel_small_mixed_all_widths(torch_cuda, mrhs, m):
     assert np.all(err <= 1e-5), err
 
 
+@pytest.mark.parametrize("n", [255, 257, 4097])
+@pytest.mark.parametrize("m", [2, 8, 9, 16])
+def test_mixed_column_batches(torch_cuda, mrhs, n, m):
+    """Refinement steps run for up to eight columns per launch, each column on
+    its own reduction: block widths on both sides of a batch and of two, fewer
+    rows than a workgroup's and ragged ones, and one column that takes no step.
+    A second solve, on the tickets the first one left, gives the same bits."""
+    A = grids.dirichlet7(n, 1, 1)
+    B = rng.rhs_block(n, m, 40 + m)
+    B[:, 0] = 0.0
+    X, infos, st = gpu_solve(mrhs, torch_cuda, A, B, mixed=True, tol=1e-10)
+    assert st == 0, infos
+    assert np.all(true_relres(A, X, B) <= 1e-10)
+    assert np.all(X[:, 0] == 0.0)
+    X2, infos2, _ = gpu_solve(mrhs, torch_cuda, A, B, mixed=True, tol=1e-10)
+    assert infos == infos2
+    assert np.array_equal(X, X2)
+
+
 def test_mixed_nan_and_zero_columns_isolated(torch_cuda, mrhs):
     """Mixed precision: a zero right-hand side returns x = 0 at once, a NaN
     column fails alone, and the other columns still converge."""
