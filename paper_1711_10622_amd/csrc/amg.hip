@@ -725,7 +725,7 @@ void attach_dict(mrhs_amg_s *H, const amg::HostCsr &C, const std::vector<double>
     dict::Codes<double> c1;
     if (!vah.empty())
         c1 = dict::codes<double>(C.nr, nnz, C.rp.data(), C.ci.data(), vah.data(), offs);
-    if (offs.ok && c0.ok && c1.ok && C.nr >= kPatMinRows && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
+    if (offs.ok && c0.ok && c1.ok && pattern_rows(C.nr) && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
         const dict::Patterns p = dict::patterns(C.nr, C.rp.data(), c0.code.data(), c1.code.data());
         if (p.ok) {
             const uint16_t *pid = upload(H, p.id.data(), p.id.size(), 0, err);

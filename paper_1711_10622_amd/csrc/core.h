@@ -455,6 +455,13 @@ constexpr int kPatEntries = 1 << 15;  // and this many table entries
 constexpr int kPatRowsPer = 8;        // and this many rows per pattern on average
 constexpr int32_t kPatMinRows = 16384;  // sizes at which products change form
 constexpr int32_t kPatRows = 1 << 21;   // (pattern_pays)
+// The pattern products compute, in 32 bits, the end of a tile and rows up to a
+// pass, a wave and the row beside it past a row of the matrix, before they
+// limit them to it.  Matrices so large that these could pass 2^31 - 1 have no
+// patterns and read codes, whose products add nothing to a row's index.
+constexpr int32_t kPatMaxRows = INT32_MAX - 1024;
+static_assert(kPatMaxRows <= INT32_MAX - (kTileRows + kBlock + 64 + 1), "row indexes of the pattern products");
+constexpr bool pattern_rows(int32_t n) { return n >= kPatMinRows && n <= kPatMaxRows; }
 
 template <typename T>
 struct CsrView {

@@ -353,7 +353,7 @@ mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, cons
         return set_error(MRHS_EDEVICE, "read-back failed: %s", hipGetErrorString(e));
     const dict::Codes<double> c0 = dict::codes<double>(A->n, A->nnz, rp, ci, sval, offs);
     const dict::Codes<double> c1 = dict::codes<double>(A->n, A->nnz, rp, ci, h.data(), offs);
-    if (offs.ok && c0.ok && c1.ok && A->n >= kPatMinRows && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
+    if (offs.ok && c0.ok && c1.ok && pattern_rows(A->n) && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
         const dict::Patterns p = dict::patterns(A->n, rp, c0.code.data(), c1.code.data());
         if (p.ok) {
             if ((st = upload_vec(&A->plen, p.len, total)) ||
