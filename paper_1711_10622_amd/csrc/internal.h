@@ -265,26 +265,51 @@ inline int split_slots(int32_t avg, int row_slots)
 }
 
 // Whether a product over n rows reads the row patterns of a matrix that has
-// them (else its codes).  Measured as kernel time, codes -> patterns:
-//  * plain products (no reduction) of kPatMinRows to kPatRows rows, and of
-//    narrow rows above: 938k-row channel (131x77x93) m = 1 25.9 -> 23.6 us, m =
-//    4 35 -> 28, m = 7 53 -> 48, m = 8 47 -> 40, binary32 m = 16 47 -> 39;
-//    12.6M-row channel m = 1 139 -> 111, m = 2 181 -> 129.  Wider rows of
-//    larger matrices wait for block rows, not for the matrix, and gain nothing
+// them (else its codes).  Measured, codes -> patterns:
+//  * plain products (no reduction) from pattern_min_rows to kPatRows rows, and
+//    of narrow rows above: 938k-row channel (131x77x93) m = 1 25.5 -> 23.1 us,
+//    m = 4 35.5 -> 29.5, m = 7 54 -> 48, m = 8 48 -> 40, binary32 m = 16 45 ->
+//    39; 2.08M rows m = 8 87 -> 68, m = 16 157 -> 147; 12.6M-row channel m = 1
+//    139 -> 105, m = 2 181 -> 118.  Wider rows of larger matrices wait for
+//    block rows, not for the matrix: on the 12.6M-row channel they gain nothing
 //    from waves that run further apart (m = 4 317 -> 306, m = 7 661 -> 725, m =
-//    8 525 -> 533); nor do small matrices, whose short grid lines leave few
-//    waves with one pattern (16^3, m = 16: 10.8 -> 13.0);
+//    8 525 -> 533); between 2.1 and 6.3M rows only the codes were measured;
 //  * two blocks gathered per entry past kPatRows: spmv_omega on the 12.6M-row
 //    channel m = 4 500 -> 448 us, m = 8 928 -> 849, m = 16 1790 -> 1651; on the
 //    524k-row one it is no faster (m = 4 28.0 -> 29.7, m = 16 79.2 -> 81.4);
 //  * the others never: spmv_sigma on the 524k-row channel m = 4 20.5 -> 22.9,
 //    32^3 m = 16 11.0 -> 11.6, xr_sigma m = 4 51 -> 55.
+//
+// Rows of a plain product from which patterns pay.  A wave whose rows have
+// several patterns (at the ends of grid lines) gathers four entries at a time
+// through vector loads of the table, which costs most where many lanes share a
+// row and on matrices of few waves.  Speedup over codes (captured graphs of 40
+// products) at 20k / 49k / 111k / 184k / 295k / 390k / 524k / 819k rows:
+//  * binary64 rows of one-element lanes, m = 5 .96 / .94 / .94 / .99 / .98 /
+//    1.05 / 1.13 / 1.16, m = 7 .92 / .99 / .98 / .99 / .99 / 1.05 / 1.08 /
+//    1.15, m = 9 .91 / 1.00 / 1.01 / 1.03 / .98 / .97 / 1.02 / 1.03; of 13 and
+//    15 columns, four rows to a wave, m = 13 .99 / .97 / .95 / 1.01 / .91 / 1.00
+//    / 1.01 / .91 and 1.02 at 2.08M: never;
+//  * five lanes to a row, m = 10 1.00 / .97 / .96 / 1.02 / .99 / 1.09 / 1.06 /
+//    1.13, binary32 m = 5 .99 / .98 / .96 / 1.03 / 1.04 / 1.08 / 1.14 / 1.17;
+//  * the others, m = 1 1.04 / 1.00 / 1.01 / .98 / .98 / 1.01 / 1.04 / 1.02, m =
+//    16 1.05 / 1.03 / 1.03 / 1.07 / .97 / 1.07 / 1.08 / 1.02, binary32 m = 11
+//    1.05 / 1.05 / 1.04 / 1.10 / 1.16 / 1.01 / 1.08 / 1.20.
+template <typename T, int M>
+constexpr int32_t pattern_min_rows()
+{
+    using S = Shape<T, M>;
+    if (M > 1 && S::VW == 1 && sizeof(T) == 8)
+        return S::RW == 4 ? INT32_MAX : S::RW < 8 ? 1 << 19 : 5 << 16;
+    return S::L == 5 ? 1 << 17 : kPatMinRows;
+}
+
 template <typename T, int M, class Op>
 inline bool pattern_pays(int32_t n)
 {
     if (gathered_blocks<Op>::value == 2)
         return n > kPatRows;
-    if (gathered_blocks<Op>::value != 1 || Op::NDOT > 0 || n < kPatMinRows)
+    if (gathered_blocks<Op>::value != 1 || Op::NDOT > 0 || n < pattern_min_rows<T, M>())
         return false;
     return n <= kPatRows || Shape<T, M>::ROW_BYTES <= 16;
 }
