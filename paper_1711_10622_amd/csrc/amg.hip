@@ -685,12 +685,18 @@ CsrView<double> upload_csr(mrhs_amg_s *H, const amg::HostCsr &C, const std::vect
 }
 
 // The dictionary form (16-bit or column codes, value table) of a level
-// operator's binary64 view v, when it has one; otab: the level's offset table
-// on the device (16-bit codes).
-void attach_codes(mrhs_amg_s *H, const dict::Codes<double> &c, const dict::Offsets &offs, const int32_t *otab,
-                  CsrView<double> &v, hipError_t *err)
+// operator's binary64 view v with values vals, when it has one; otab: the
+// level's offset table on the device (16-bit codes).  Levels have no row
+// patterns: on the finest level, the one they could serve, the smoothing sweep
+// took 1-5 % longer from patterns than from codes (channels of 128,000 to 2.08M
+// rows, binary64, nearly every block width) and the residual was within 1 %.
+void attach_dict(mrhs_amg_s *H, const amg::HostCsr &C, const std::vector<double> &vals, const dict::Offsets &offs,
+                 const int32_t *otab, CsrView<double> &v, hipError_t *err)
 {
-    if (*err != hipSuccess || !c.ok)
+    if (*err != hipSuccess)
+        return;
+    const dict::Codes<double> c = dict::codes<double>(C.nr, C.nnz(), C.rp.data(), C.ci.data(), vals.data(), offs);
+    if (!c.ok)
         return;
     const double *tab = upload(H, c.tab.data(), c.tab.size(), 0, err);
     if (offs.ok) {
@@ -712,44 +718,6 @@ void attach_codes(mrhs_amg_s *H, const dict::Codes<double> &c, const dict::Offse
     v.nvals = static_cast<int32_t>(c.tab.size());
 }
 
-// The forms of a level's operator and (vah not empty) of A_l D_l1^-1, as
-// csr_create chooses them: row patterns where the coded rows repeat, else
-// codes.
-void attach_dict(mrhs_amg_s *H, const amg::HostCsr &C, const std::vector<double> &vah, AmgLevelDev &d,
-                 hipError_t *err)
-{
-    const int64_t nnz = C.nnz();
-    dict::Offsets offs;
-    dict::offsets(C.nr, C.rp.data(), C.ci.data(), offs);
-    const dict::Codes<double> c0 = dict::codes<double>(C.nr, nnz, C.rp.data(), C.ci.data(), C.va.data(), offs);
-    dict::Codes<double> c1;
-    if (!vah.empty())
-        c1 = dict::codes<double>(C.nr, nnz, C.rp.data(), C.ci.data(), vah.data(), offs);
-    if (offs.ok && c0.ok && c1.ok && pattern_rows(C.nr) && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
-        const dict::Patterns p = dict::patterns(C.nr, C.rp.data(), c0.code.data(), c1.code.data());
-        if (p.ok) {
-            const uint16_t *pid = upload(H, p.id.data(), p.id.size(), 0, err);
-            const int32_t *plen = upload(H, p.len.data(), p.len.size(), 0, err);
-            CsrView<double> *views[2] = {&d.A, &d.Ah};
-            const double *vals[2] = {C.va.data(), vah.data()};
-            for (int k = 0; k < 2; ++k) {
-                const auto tab = dict::pattern_table(p, C.rp.data(), C.ci.data(), vals[k]);
-                const auto st = dict::stencil_table(p, tab);
-                views[k]->pent = upload(H, tab.data(), tab.size(), 0, err);
-                views[k]->pst = upload(H, st.data(), st.size(), 0, err);
-                views[k]->pid = *err == hipSuccess ? pid : nullptr;
-                views[k]->plen = plen;
-                views[k]->pk = p.pk;
-                views[k]->npat = static_cast<int32_t>(p.rep.size());
-            }
-        }
-    }
-    std::vector<int32_t> otab(offs.set.keys.begin(), offs.set.keys.end());
-    const int32_t *dotab = offs.ok ? upload(H, otab.data(), otab.size(), 0, err) : nullptr;
-    attach_codes(H, c0, offs, dotab, d.A, err);
-    attach_codes(H, c1, offs, dotab, d.Ah, err);
-}
-
 void free_amg(mrhs_amg_s *H)
 {
     if (!H)
@@ -764,26 +732,6 @@ __global__ void k_round32(const double *__restrict__ src, float *__restrict__ ds
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; k < count;
          k += static_cast<int64_t>(gridDim.x) * blockDim.x)
         dst[k] = static_cast<float>(src[k]);
-}
-
-__global__ void k_round_table(const PatEntry<double> *__restrict__ src, PatEntry<float> *__restrict__ dst,
-                              int32_t count, const PatStencil<double> *__restrict__ ssrc,
-                              PatStencil<float> *__restrict__ sdst, int32_t npat)
-{
-    const int32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count)
-        dst[k] = PatEntry<float>{static_cast<float>(src[k].v), src[k].off};
-    if (k < npat) {
-        PatStencil<float> s{};
-        for (int f = 0; f < kFar; ++f) {
-            s.fv[f] = static_cast<float>(ssrc[k].fv[f]);
-            s.fo[f] = ssrc[k].fo[f];
-        }
-        for (int f = 0; f < 3; ++f)
-            s.nv[f] = static_cast<float>(ssrc[k].nv[f]);
-        s.meta = ssrc[k].meta;
-        sdst[k] = s;
-    }
 }
 
 // binary32 rounding (nearest even) of count device values, padding included
@@ -807,7 +755,7 @@ float *round32(mrhs_amg_s *H, const double *src, int64_t count, hipError_t *err)
 }
 
 // The binary32 view of a level operator: its values rounded (nearest even);
-// a binary64 dictionary or row-pattern form carries over with its values rounded the
+// a binary64 dictionary form carries over with its value table rounded the
 // same way (equal values round alike, so each entry's code still names its
 // rounded value; the table may then hold repeats).
 CsrView<float> view32(mrhs_amg_s *H, const CsrView<double> &v, int64_t nnz, hipError_t *err)
@@ -825,30 +773,6 @@ CsrView<float> view32(mrhs_amg_s *H, const CsrView<double> &v, int64_t nnz, hipE
             w.ccode = v.ccode;
             w.cb = v.cb;
         }
-    }
-    if (v.pid && *err == hipSuccess) {
-        void *p = nullptr, *q = nullptr;
-        const int32_t count = v.npat * v.pk;
-        const size_t be = sizeof(PatEntry<float>) * static_cast<size_t>(count);
-        const size_t bs = sizeof(PatStencil<float>) * static_cast<size_t>(v.npat);
-        if ((*err = hipMalloc(&p, be)) != hipSuccess)
-            return w;
-        H->allocs.push_back(p);
-        if ((*err = hipMalloc(&q, bs)) != hipSuccess)
-            return w;
-        H->allocs.push_back(q);
-        H->bytes += be + bs;
-        hipLaunchKernelGGL(k_round_table, dim3(static_cast<unsigned>((count + 255) / 256)), dim3(256), 0, nullptr,
-                           v.pent, static_cast<PatEntry<float> *>(p), count, v.pst,
-                           static_cast<PatStencil<float> *>(q), v.npat);
-        if ((*err = hipGetLastError()) != hipSuccess)
-            return w;
-        w.pid = v.pid;
-        w.pent = static_cast<const PatEntry<float> *>(p);
-        w.pst = static_cast<const PatStencil<float> *>(q);
-        w.plen = v.plen;
-        w.pk = v.pk;
-        w.npat = v.npat;
     }
     return w;
 }
@@ -963,11 +887,18 @@ MRHS_API mrhs_status amg_create(mrhs_csr A, double theta, int32_t max_coarse, in
             d.nnz_p = hl.P.nnz();
             H->cf.push_back(hl.cf);
         }
-        // the tiled products of A_l and A_l D_l1^-1 read row patterns or codes
-        // where the level's operator has such a form (MRHS_CSR_DICT=0: never);
+        // the tiled products of A_l and A_l D_l1^-1 read codes where the
+        // level's operator has a dictionary form (MRHS_CSR_DICT=0: never);
         // the iteration's own products with A_0 are tiled at every size
-        if (use_dict && (l == 0 || !d.A.split) && hl.A.nnz() > 0 && e == hipSuccess)
-            attach_dict(H, hl.A, vah, d, &e);
+        if (use_dict && (l == 0 || !d.A.split) && hl.A.nnz() > 0 && e == hipSuccess) {
+            dict::Offsets offs;
+            dict::offsets(hl.A.nr, hl.A.rp.data(), hl.A.ci.data(), offs);
+            std::vector<int32_t> otab(offs.set.keys.begin(), offs.set.keys.end());
+            const int32_t *dotab = offs.ok ? upload(H, otab.data(), otab.size(), 0, &e) : nullptr;
+            attach_dict(H, hl.A, hl.A.va, offs, dotab, d.A, &e);
+            if (l + 1 < L)
+                attach_dict(H, hl.A, vah, offs, dotab, d.Ah, &e);
+        }
         if (e != hipSuccess)
             break;
     }

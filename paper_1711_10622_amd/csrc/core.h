@@ -481,11 +481,10 @@ struct CsrView {
     int32_t cb = 0;  // bits of the column in a column code
     // row-pattern form (gspmv_tiles_pat; null pid: one of the forms above)
     const uint16_t *__restrict__ pid = nullptr;   // [n] pattern of each row
-    const PatEntry<T> *__restrict__ pent = nullptr;  // [npat * pk] entries, pk per pattern
-    const int32_t *__restrict__ plen = nullptr;   // [npat] entries of each pattern
-    const PatStencil<T> *__restrict__ pst = nullptr;  // [npat]
+    const PatEntry<T> *__restrict__ pent = nullptr;  // [patterns * pk] entries, pk per pattern
+    const int32_t *__restrict__ plen = nullptr;   // [patterns] entries of each pattern
+    const PatStencil<T> *__restrict__ pst = nullptr;  // [patterns]
     int32_t pk = 0;    // room for whole batches of kPatBatch and MRHS_GATHER_BATCH
-    int32_t npat = 0;
 };
 
 // One row of the product: sum over the row's entries in storage order of
