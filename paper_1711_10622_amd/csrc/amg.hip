@@ -669,6 +669,13 @@ int32_t median_reach(const amg::HostCsr &A)
 // against 388 and 801 us; with only levels of 12 and more entries per row on
 // it, 395 and 807 us.
 constexpr int32_t kSplitMaxRows = 131072;
+// Short rows of such a level are coded all the same: the block widths whose
+// lanes do not fill a wave run the tiled product at every size, and short rows
+// gain from codes there (V-cycle of the 300 x 300 plane, levels of 90,000 to
+// 119 rows with 5 to 20 entries each: m = 3 294 us from the plain arrays, 279
+// from codes, m = 5 364 and 355, m = 7 429 and 420).  From this many entries
+// per row on, the plain arrays were as fast.
+constexpr int32_t kCodedRowNnz = 12;
 
 CsrView<double> upload_csr(mrhs_amg_s *H, const amg::HostCsr &C, const std::vector<double> *vals, int32_t reach,
                            hipError_t *err)
@@ -890,7 +897,7 @@ MRHS_API mrhs_status amg_create(mrhs_csr A, double theta, int32_t max_coarse, in
         // the tiled products of A_l and A_l D_l1^-1 read codes where the
         // level's operator has a dictionary form (MRHS_CSR_DICT=0: never);
         // the iteration's own products with A_0 are tiled at every size
-        if (use_dict && (l == 0 || !d.A.split) && hl.A.nnz() > 0 && e == hipSuccess) {
+        if (use_dict && (l == 0 || d.A.split < kCodedRowNnz) && hl.A.nnz() > 0 && e == hipSuccess) {
             dict::Offsets offs;
             dict::offsets(hl.A.nr, hl.A.rp.data(), hl.A.ci.data(), offs);
             std::vector<int32_t> otab(offs.set.keys.begin(), offs.set.keys.end());

@@ -60,3 +60,21 @@ def test_levels_read_codes(env, name, m):
         assert np.array_equal(a, b)
     for h in (H, F, M, N):
         h.close()
+
+
+def test_short_rows_of_small_levels_are_coded(env):
+    """Plane of 300 x 300: the second level, 45,000 rows of nine entries, is
+    coded beside the first (2 bytes per entry of A_l and of A_l D_l1^-1), and
+    widths that run tiled there (3, 5, 7, 9) give the plain arrays' bits."""
+    torch, p = env
+    A = grids.dirichlet7(300, 300, 1)
+    (M, H), (N, F) = hierarchy(p, A), hierarchy(p, A, MRHS_CSR_DICT="0")
+    n1, nnz1 = H.level(1)[:2]
+    assert n1 < 131072 and nnz1 < 12 * n1
+    assert H.device_bytes - F.device_bytes >= 4 * (A.nnz + nnz1)
+    for m in (3, 5, 7, 9):
+        B = rng.rhs_block(A.n, m, 950 + m)
+        for a, b in zip(vcycles(torch, H, B), vcycles(torch, F, B)):
+            assert np.array_equal(a, b)
+    for h in (H, F, M, N):
+        h.close()
