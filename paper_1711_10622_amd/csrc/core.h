@@ -63,6 +63,10 @@ constexpr int kTileRows = MRHS_TILE_ROWS;  // rows per tile (at least one pass)
 constexpr int kGroups = 8;
 constexpr int kMaxM = 16;
 constexpr int kMaxDots = 8;  // largest NDOT of any reduction (GCR projections)
+// Most partial sums of one workgroup in any launch (NDOT * M, times the columns
+// of a launch over several).  The buffer has room for kMaxDots * kMaxM; what
+// lies past kRedValues per workgroup holds live ticket counters.
+constexpr int kRedValues = 64;
 
 constexpr int next_pow2(int x) { return x <= 1 ? 1 : 2 * next_pow2((x + 1) / 2); }
 
@@ -1807,6 +1811,7 @@ __device__ __forceinline__ void grid_reduce(Acc<T, Shape<T, M>::VW, NDOT> &acc, 
 {
     using S = Shape<T, M>;
     constexpr int V = NDOT * M;
+    static_assert(V <= kRedValues, "partial sums would run into the column tickets");
     constexpr int TPV = (kBlock / V) > 64 ? 64 : (kBlock / V); // threads per value
     __shared__ T s_w[kBlock / 64][V];
     __shared__ T s_k[TPV][V];

@@ -215,6 +215,7 @@ __global__ void __launch_bounds__(kBlock) k_stream(int32_t n, Op op, RedBufs<T> 
 template <class Op>
 __global__ void __launch_bounds__(kBlock) k_cols(ColBatch cb, RedBufs<double> rb, TilePlan plan)
 {
+    static_assert(kColBatch * Op::NDOT <= kRedValues, "partial sums would run into the column tickets");
     const int y = blockIdx.y;
     const Op op = cb.op<Op>(y);
     const RedBufs<double> mine{rb.part + static_cast<size_t>(y) * gridDim.x * Op::NDOT,

@@ -116,10 +116,9 @@ Layout layout(int32_t n, int32_t m, uint32_t flags, const AmgDev *amg = nullptr)
     L.ctl = take(sizeof(Ctl));
     L.kry64 = take(sizeof(Kry<double>));
     L.kry32 = take(sizeof(Kry<float>));
-    // the partial sums have room for kMaxDots dots of kMaxM columns, twice what
-    // any reduction has (four dots of kMaxM columns; kMaxDots of each of
-    // kColBatch columns); the ticket counters' lines are taken out of it, those
-    // of k_cols lie at the start of its second half
+    // the partial sums have room for kMaxDots dots of kMaxM columns, twice the
+    // kRedValues any launch has; the ticket counters' lines are taken out of it,
+    // those of k_cols lie at the start of its second half
     const size_t V = static_cast<size_t>(kMaxDots) * kMaxM;
     static_assert(sizeof(unsigned) * kTicketStride % kAlign == 0, "a counter fills whole lines");
     L.tickets = take(sizeof(unsigned) * kTicketStride * (kGroups + 1));
@@ -463,10 +462,9 @@ Engine::Engine(const mrhs_csr_s &A, int m, uint32_t flags, void *ws, const doubl
     tickets_ = reinterpret_cast<unsigned *>(base + L.tickets);
     c_.rb64 = {reinterpret_cast<double *>(base + L.part), reinterpret_cast<double *>(base + L.gpart), tickets_};
     c_.rb32 = {reinterpret_cast<float *>(base + L.part), reinterpret_cast<float *>(base + L.gpart), tickets_};
-    const size_t half = static_cast<size_t>(kMaxDots) * kMaxM / 2 * static_cast<size_t>(max_grid());
-    static_assert(kMaxDots * kColBatch <= kMaxDots * kMaxM / 2, "partial sums of k_cols fit the first half");
-    static_assert(kMaxDots * kColBatch <= kMaxDots * kMaxM, "and the groups' sums their room");
-    col_tickets_ = reinterpret_cast<unsigned *>(c_.rb64.part + half);
+    // the tickets of k_cols lie past the sums of any launch
+    static_assert(2 * kRedValues <= kMaxDots * kMaxM, "and leave them as much room");
+    col_tickets_ = reinterpret_cast<unsigned *>(c_.rb64.part + static_cast<size_t>(kRedValues) * max_grid());
     c_.rbcol = {c_.rb64.part, c_.rb64.gpart, col_tickets_};
     ndirs_ = gcr_dirs();
     if (mixed_) {
