@@ -73,10 +73,8 @@ struct OpVcStore {
     const Ctl *ctl;
     using Lane = VcLane;
     __device__ Lane lane(int g) const { return {lane_running<T, M>(ctl, g)}; }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const { ld<T, M>(X, c, g, x); }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &, Row i, int g, const T *sum, Acc<T, S::VW, NDOT> &) const
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const { ld<T, M>(X, c, g, x); }
+    __device__ __forceinline__ void row(const Lane &, int32_t i, int g, const T *sum, Acc<T, S::VW, NDOT> &) const
     {
         st<T, M>(Y, i, g, sum);
     }
@@ -96,20 +94,17 @@ struct OpVcRes {
     const Ctl *ctl;
     using Lane = VcLane;
     __device__ Lane lane(int g) const { return {lane_running<T, M>(ctl, g)}; }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const { ld<T, M>(X, c, g, x); }
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const { ld<T, M>(X, c, g, x); }
     struct Pre {
         T u[S::VW];
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
     {
         Pre pr;
         ld<T, M>(U, i, g, pr.u);
         return pr;
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &, Row i, int g, const T *sum, Acc<T, S::VW, NDOT> &,
+    __device__ __forceinline__ void row(const Lane &, int32_t i, int g, const T *sum, Acc<T, S::VW, NDOT> &,
                                         const Pre &pr) const
     {
         T u[S::VW];
@@ -133,22 +128,19 @@ struct OpVcProl {
     const Ctl *ctl;
     using Lane = VcLane;
     __device__ Lane lane(int g) const { return {lane_running<T, M>(ctl, g)}; }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const { ld<T, M>(X, c, g, x); }
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const { ld<T, M>(X, c, g, x); }
     struct Pre {
         T u[S::VW];
         T d;
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
     {
         Pre pr;
         ld<T, M>(U, i, g, pr.u);
         pr.d = dinv[i];
         return pr;
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &, Row i, int g, const T *sum, Acc<T, S::VW, NDOT> &,
+    __device__ __forceinline__ void row(const Lane &, int32_t i, int g, const T *sum, Acc<T, S::VW, NDOT> &,
                                         const Pre &pr) const
     {
         T u[S::VW];
@@ -172,14 +164,12 @@ struct OpVcSmooth {
     const Ctl *ctl;
     using Lane = VcLane;
     __device__ Lane lane(int g) const { return {lane_running<T, M>(ctl, g)}; }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const { ld<T, M>(Tv, c, g, x); }
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const { ld<T, M>(Tv, c, g, x); }
     struct Pre {
         T t[S::VW], u[S::VW];
         T d;
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
     {
         Pre pr;
         ld<T, M>(Tv, i, g, pr.t);
@@ -187,8 +177,7 @@ struct OpVcSmooth {
         pr.d = dinv[i];
         return pr;
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &, Row i, int g, const T *sum, Acc<T, S::VW, NDOT> &,
+    __device__ __forceinline__ void row(const Lane &, int32_t i, int g, const T *sum, Acc<T, S::VW, NDOT> &,
                                         const Pre &pr) const
     {
         T t[S::VW];
@@ -295,23 +284,20 @@ struct OpSpmv2P : OpSpmv2<double, M> {
     using Base = OpSpmv2<double, M>;
     using S = Shape<double, M>;
     using Lane = typename Base::Lane;
-    static constexpr bool kPreOwn = false;  // s is not what is gathered
+    static constexpr bool kPatterns = false;
     const double *sh;  // M^-1 s, gathered
     const double *sv;  // s
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, double *x) const { ld<double, M>(sh, c, g, x); }
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, double *x) const { ld<double, M>(sh, c, g, x); }
     struct Pre {
         double s[S::VW];
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
     {
         Pre pr;
         ld<double, M>(sv, i, g, pr.s);
         return pr;
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const double *sum,
+    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const double *sum,
                                         Acc<double, S::VW, Base::NDOT> &acc, const Pre &pr) const
     {
         const double *s = pr.s;

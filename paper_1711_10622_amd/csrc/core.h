@@ -918,12 +918,13 @@ __device__ __forceinline__ void gspmv_tiles_cc(const CsrView<T> &A, const Op &op
     }
 }
 
-// Ops whose Pre repeats what they gather at their own row may set kPreOwn =
-// true and declare pre_own(lane, row, g, own) taking it from there.
+// Ops whose products may read row patterns set kPatterns = true and take both
+// kinds of row; without a reduction they have no Pre, with two blocks gathered
+// per entry pre_own gives it from the row's own gathered values.
 template <class Op, class = void>
-struct has_pre_own : std::false_type {};
+struct reads_patterns : std::false_type {};
 template <class Op>
-struct has_pre_own<Op, std::void_t<decltype(Op::kPreOwn)>> : std::integral_constant<bool, Op::kPreOwn> {};
+struct reads_patterns<Op, std::void_t<decltype(Op::kPatterns)>> : std::integral_constant<bool, Op::kPatterns> {};
 
 #define MRHS_CONST_AS __attribute__((address_space(4)))
 
@@ -1025,10 +1026,6 @@ __device__ __forceinline__ void gspmv_tiles_pat(const CsrView<T> &A, const Op &o
 #pragma unroll
             for (int v = 0; v < VW; ++v)
                 sum[v] = T(0);
-            [[maybe_unused]] typename pre_of<Op>::type pr{};
-            if constexpr (has_pre<Op>::value)
-                if (on)
-                    pr = op.pre(ln, row, g);
             auto batch = [&](const PatBatch<T> &b, int j) {
                 T x[NB][VW];
 #pragma unroll
@@ -1066,12 +1063,8 @@ __device__ __forceinline__ void gspmv_tiles_pat(const CsrView<T> &A, const Op &o
                                        sum);
             }
             asm volatile("" : "+v"(pid_next));  // waited for before the store: later, a wait would be for the store too
-            if (on) {
-                if constexpr (has_pre<Op>::value)
-                    op.row(ln, row, g, sum, acc, pr);
-                else
-                    op.row(ln, row, g, sum, acc);
-            }
+            if (on)
+                op.row(ln, row, g, sum, acc);
             pid = pid_next;
         }
     }
@@ -1154,7 +1147,6 @@ __device__ __forceinline__ void gspmv_near_pat(const CsrView<T> &A, const Op &op
 #pragma unroll
             for (int v = 0; v < VW; ++v)
                 sum[v] = T(0);
-            [[maybe_unused]] typename pre_of<Op>::type pr{};
             if (stencil && p0 != loaded) {
                 const auto *e = (const MRHS_CONST_AS PatStencil<T> *)(A.pst) + p0;
 #pragma unroll
@@ -1169,12 +1161,7 @@ __device__ __forceinline__ void gspmv_near_pat(const CsrView<T> &A, const Op &op
                 loaded = p0;
             }
             stencil = stencil && meta != 0;
-            if (on) {
-                if constexpr (has_pre_own<Op>::value)
-                    pr = op.pre_own(ln, row, g, own);
-                else if constexpr (has_pre<Op>::value)
-                    pr = op.pre(ln, row, g);
-            }
+            const typename Op::Pre pr = op.pre_own(own);
             if (stencil) {
                 T x[kFar][VW];
 #pragma unroll
@@ -1228,12 +1215,8 @@ __device__ __forceinline__ void gspmv_near_pat(const CsrView<T> &A, const Op &op
 #pragma unroll
             for (int v = 0; v < VW; ++v)
                 asm volatile("" : "+v"(own_next[v]), "+v"(side_next[v]), "+v"(pid_next));
-            if (on) {
-                if constexpr (has_pre<Op>::value)
-                    op.row(ln, row, g, sum, acc, pr);
-                else
-                    op.row(ln, row, g, sum, acc);
-            }
+            if (on)
+                op.row(ln, row, g, sum, acc, pr);
 #pragma unroll
             for (int v = 0; v < VW; ++v) {
                 own[v] = own_next[v];

@@ -305,14 +305,21 @@ constexpr int32_t pattern_min_rows()
     return S::L == 5 ? 1 << 17 : kPatMinRows;
 }
 
+// The part the op and the block width decide: whether there is a kernel.
+template <typename T, int M, class Op>
+constexpr bool has_pattern_kernel()
+{
+    return reads_patterns<Op>::value && (gathered_blocks<Op>::value == 2 || pattern_min_rows<T, M>() < INT32_MAX);
+}
+
 template <typename T, int M, class Op>
 inline bool pattern_pays(int32_t n)
 {
+    if (!has_pattern_kernel<T, M, Op>())
+        return false;
     if (gathered_blocks<Op>::value == 2)
         return n > kPatRows;
-    if (gathered_blocks<Op>::value != 1 || Op::NDOT > 0 || n < pattern_min_rows<T, M>())
-        return false;
-    return n <= kPatRows || Shape<T, M>::ROW_BYTES <= 16;
+    return n >= pattern_min_rows<T, M>() && (n <= kPatRows || Shape<T, M>::ROW_BYTES <= 16);
 }
 
 template <typename T, int M, class Op>
@@ -346,23 +353,28 @@ inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<
     const TilePlan plan =
         tile_plan(A.n, tile_passes<T, M, Op>(A.n), Shape<T, M>::RPP, A.reach,
                   (gathered_blocks<Op>::value + 1) * M * static_cast<int32_t>(sizeof(T)));
-    const bool pat = A.pid && pattern_pays<T, M, Op>(A.n);
-    // a product with a reduction runs on the staged kernel's grid in every
-    // form, so that partial dot products do not depend on the form.  Else row
-    // patterns, which need no LDS, fit up to eight workgroups on a CU; more
-    // than four send wide rows' tiles in flight out of an XCD's L2 (12.6M-row
-    // channel, m = 8: 533 -> 553 us)
-    const void *fn = pat && Op::NDOT == 0 ? reinterpret_cast<const void *>(&k_gspmv_pat<T, M, Op>)
-                                          : reinterpret_cast<const void *>(&k_gspmv<T, M, Op>);
-    const int most = max_per_cu<Op>::value                                   ? max_per_cu<Op>::value
-                     : pat && Op::NDOT == 0 && Shape<T, M>::ROW_BYTES >= 64 ? 4
-                                                                             : 0;
+    const void *fn = reinterpret_cast<const void *>(&k_gspmv<T, M, Op>);
+    auto *kernel = &k_gspmv<T, M, Op>;
+    int most = max_per_cu<Op>::value;
+    if constexpr (has_pattern_kernel<T, M, Op>()) {
+        if (A.pid && pattern_pays<T, M, Op>(A.n)) {
+            kernel = &k_gspmv_pat<T, M, Op>;
+            // a product with a reduction runs on the staged kernel's grid in
+            // every form, so that partial dot products do not depend on the
+            // form.  Else row patterns, which need no LDS, fit up to eight
+            // workgroups on a CU; more than four send wide rows' tiles in
+            // flight out of an XCD's L2 (12.6M-row channel, m = 8: 533 -> 553
+            // us)
+            if (Op::NDOT == 0) {
+                fn = reinterpret_cast<const void *>(kernel);
+                if (most == 0 && Shape<T, M>::ROW_BYTES >= 64)
+                    most = 4;
+            }
+        }
+    }
     const int grid = grid_for(fn, A.n, Shape<T, M>::RPP * plan.passes, most);
     const int slot = g_trace_every ? trace_begin(s, Op::kName, static_cast<int>(sizeof(T)), M, grid) : -1;
-    if (pat)
-        hipLaunchKernelGGL((k_gspmv_pat<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
-    else
-        hipLaunchKernelGGL((k_gspmv<T, M, Op>), dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, s, A, op, rb, plan);
     if (slot >= 0)
         trace_end(slot, s);
     return hipGetLastError();

@@ -177,6 +177,7 @@ struct OpStore {
     static constexpr const char *kName = "gspmv";
     using S = Shape<T, M>;
     static constexpr int NDOT = 0;
+    static constexpr bool kPatterns = true;
     const T *X;
     T *Y;
     struct Lane {
@@ -261,8 +262,7 @@ struct OpResid {
         }
         return ln;
     }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, double *x) const
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, double *x) const
     {
         ld<double, M>(X, c, g, x);
     }
@@ -270,15 +270,13 @@ struct OpResid {
     struct Pre {
         double b[S::VW];
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
     {
         Pre pr;
         ld<double, M>(B, i, g, pr.b);
         return pr;
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const double *sum,
+    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const double *sum,
                                         Acc<double, S::VW, NDOT> &acc, const Pre &pr) const
     {
         const size_t o = static_cast<size_t>(i) * M + g * S::VW;
@@ -476,13 +474,11 @@ struct OpSpmv1 {
     int32_t ldp;  // row stride of v
     using Lane = RunLane<T, M>;
     __device__ Lane lane(int g) const { return run_lane<T, M>(ctl, g); }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &, Row c, int g, T *x) const
+    __device__ __forceinline__ void gather(const Lane &, int32_t c, int g, T *x) const
     {
         ld<T, M>(p, c, g, x);
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const T *sum,
+    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const T *sum,
                                         Acc<T, S::VW, NDOT> &acc) const
     {
         T h[S::VW];
@@ -509,6 +505,7 @@ struct OpSpmv2 {
     static constexpr const char *kName = "spmv_omega";
     using S = Shape<T, M>;
     static constexpr int NDOT = 4;
+    static constexpr bool kPatterns = true;
 #ifndef MRHS_OMEGA_GATHERED
 #define MRHS_OMEGA_GATHERED 2
 #endif
@@ -551,16 +548,14 @@ struct OpSpmv2 {
     struct Pre {
         T s[S::VW];
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &ln, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &ln, int32_t i, int g) const
     {
         Pre pr;
         gather(ln, i, g, pr.s);
         return pr;
     }
-    static constexpr bool kPreOwn = true;
-    template <class Row>
-    __device__ __forceinline__ Pre pre_own(const Lane &, Row, int, const T *own) const
+    // the same from the row's own gathered values
+    __device__ __forceinline__ Pre pre_own(const T *own) const
     {
         Pre pr;
 #pragma unroll
@@ -802,8 +797,7 @@ struct OpXRSigma {
             pn = p;
         }
     }
-    template <class Row>
-    __device__ __forceinline__ void gather(const Lane &ln, Row c, int g, T *x) const
+    __device__ __forceinline__ void gather(const Lane &ln, int32_t c, int g, T *x) const
     {
         T rr[S::VW], vv[S::VW], tt[S::VW], pp[S::VW];
         ld<T, M>(r, c, g, rr, ldp);
@@ -819,8 +813,7 @@ struct OpXRSigma {
     struct Pre {
         T y[S::VW], r[S::VW], v[S::VW], t[S::VW], p[S::VW];
     };
-    template <class Row>
-    __device__ __forceinline__ Pre pre(const Lane &, Row i, int g) const
+    __device__ __forceinline__ Pre pre(const Lane &, int32_t i, int g) const
     {
         Pre pr;
         ld<T, M>(y, i, g, pr.y);
@@ -830,8 +823,7 @@ struct OpXRSigma {
         ld<T, M>(p, i, g, pr.p);
         return pr;
     }
-    template <class Row>
-    __device__ __forceinline__ void row(const Lane &ln, Row i, int g, const T *sum, Acc<T, S::VW, NDOT> &acc,
+    __device__ __forceinline__ void row(const Lane &ln, int32_t i, int g, const T *sum, Acc<T, S::VW, NDOT> &acc,
                                         const Pre &pr) const
     {
         T yy[S::VW], rn[S::VW], pn[S::VW], hh[S::VW];
@@ -1180,6 +1172,7 @@ struct OpColsStore {
     static constexpr const char *kName = "gcr_aw";
     using S = Shape<double, K>;
     static constexpr int NDOT = 0;
+    static constexpr bool kPatterns = true;
     const double *z[K];
     double *w[K];
     struct Lane {
