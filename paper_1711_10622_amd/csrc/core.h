@@ -487,7 +487,7 @@ struct CsrView {
     const uint16_t *__restrict__ pid = nullptr;   // [n] pattern of each row
     const PatEntry<T> *__restrict__ pent = nullptr;  // [patterns * pk] entries, pk per pattern
     const int32_t *__restrict__ plen = nullptr;   // [patterns] entries of each pattern
-    const PatStencil<T> *__restrict__ pst = nullptr;  // [patterns]
+    const PatStencil<T> *__restrict__ pst = nullptr;  // [patterns], where gspmv_near_pat reads it
     int32_t pk = 0;    // room for whole batches of kPatBatch and MRHS_GATHER_BATCH
 };
 

@@ -47,13 +47,13 @@ struct mrhs_csr_s {
     int32_t cbits[4] = {0, 0, 0, 0};
     void *vtab[4] = {nullptr, nullptr, nullptr, nullptr};
     int32_t nvals[4] = {0, 0, 0, 0};
-    // row-pattern form (CsrView::pid) of all four arrays, when the rows repeat
-    // often enough
+    // row-pattern form (CsrView::pid), when the rows repeat often enough: of
+    // arrays 0 and 2, past kPatRows rows of all four
     uint16_t *pid = nullptr;
     int32_t *plen = nullptr;
     int32_t pk = 0;
     void *pent[4] = {nullptr, nullptr, nullptr, nullptr};
-    void *pst[4] = {nullptr, nullptr, nullptr, nullptr};
+    void *pst[4] = {nullptr, nullptr, nullptr, nullptr};  // of arrays 1 and 3
 };
 
 namespace mrhs {
@@ -85,7 +85,7 @@ template <typename T>
 inline CsrView<T> view_of(const mrhs_csr_s &A, const T *va, int k)
 {
     CsrView<T> v{A.rp, A.ci, va, A.n, A.reach, 0};
-    if (A.pid) {
+    if (A.pent[k]) {
         v.pid = A.pid;
         v.pent = static_cast<const PatEntry<T> *>(A.pent[k]);
         v.pst = static_cast<const PatStencil<T> *>(A.pst[k]);

@@ -307,9 +307,9 @@ mrhs_status dict_array(mrhs_csr_s *A, const dict::Codes<V> &c, int k, size_t &to
 }
 
 // The pattern tables of binary64 value array k, and their roundings (to
-// nearest even) for the binary32 array k + 2.
+// nearest even) for the binary32 array k + 2; scaled: with their stencil shapes.
 mrhs_status pattern_arrays(mrhs_csr_s *A, const dict::Patterns &p, const std::vector<PatEntry<double>> &tab, int k,
-                           size_t &total)
+                           bool scaled, size_t &total)
 {
     PatEntry<double> *e = nullptr;
     PatEntry<float> *e32 = nullptr;
@@ -319,9 +319,9 @@ mrhs_status pattern_arrays(mrhs_csr_s *A, const dict::Patterns &p, const std::ve
     mrhs_status st = upload_vec(&e, tab, total);
     if (st == MRHS_OK)
         st = upload_vec(&e32, tab32, total);
-    if (st == MRHS_OK)
+    if (st == MRHS_OK && scaled)
         st = upload_vec(&s, dict::stencil_table(p, tab), total);
-    if (st == MRHS_OK)
+    if (st == MRHS_OK && scaled)
         st = upload_vec(&s32, dict::stencil_table(p, tab32), total);
     A->pent[k] = e;
     A->pent[k + 2] = e32;
@@ -356,9 +356,12 @@ mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, cons
     if (offs.ok && c0.ok && c1.ok && pattern_rows(A->n) && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
         const dict::Patterns p = dict::patterns(A->n, rp, c0.code.data(), c1.code.data());
         if (p.ok) {
+            // plain products read A's patterns, the omega pass past kPatRows
+            // rows those of A D^-1; no other product reads any
             if ((st = upload_vec(&A->plen, p.len, total)) ||
-                (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, sval), 0, total)) ||
-                (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, h.data()), 1, total)))
+                (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, sval), 0, false, total)) ||
+                (A->n > kPatRows &&
+                 (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, h.data()), 1, true, total))))
                 return st;
             A->pk = p.pk;
             if ((st = upload_vec(&A->pid, p.id, total)))
