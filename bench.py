@@ -66,9 +66,9 @@ def log(msg):
 def kernel_bytes(name, n, nnz, m, S, mat=None):
     """Algorithmic HBM bytes of one launch of a library kernel with all m
     columns active: each block (n x m, S bytes/element) read or written once,
-    the matrix read once: ``mat`` bytes (csr_stream_bytes: row offsets plus
-    2-byte codes in the dictionary form), by default the plain arrays (int32
-    row offsets and columns, S-byte values)."""
+    the matrix read once: ``mat`` bytes (csr_product_bytes: row patterns, or
+    row offsets plus 2-byte codes in the dictionary form), by default the plain
+    arrays (int32 row offsets and columns, S-byte values)."""
     if mat is None:
         mat = 4 * (n + 1) + (4 + S) * nnz
     blk = S * m * n
@@ -126,11 +126,14 @@ def next_pow2(x):
     return 1 if x <= 1 else 2 * next_pow2((x + 1) // 2)
 
 
-def summary_mat(A, name, S):
+def summary_mat(A, name, S, kernel=""):
     """Matrix bytes of a product kernel in an offline summary (gspmv reads A,
-    the solvers' products A D^-1)."""
+    the solvers' products A D^-1); kernel: its symbol, which tells whether it
+    read row patterns (2 bytes per row, their table of at most 0.5 MB aside)."""
     if name not in ("gspmv", "spmv_sigma", "spmv_omega"):
         return None
+    if "k_gspmv_pat<" in kernel:
+        return 2 * A.n
     return matrix_stream_bytes(A, S, scaled=name != "gspmv")
 
 
@@ -164,7 +167,7 @@ def stored_traffic(kernel):
 
 def dominant_kernel(trace, n, nnz, mats=None):
     """The kernel class with the largest estimated total time; ``mats``:
-    matrix bytes per product by element size (the solvers' scaled matrix)."""
+    matrix bytes by product and element size."""
     best = None
     for key, st in trace.items():
         name, dt, mtag, _ = key.split("/")
@@ -173,7 +176,7 @@ def dominant_kernel(trace, n, nnz, mats=None):
             best = (key, st, name, 8 if dt == "f64" else 4, int(mtag[1:]), share)
     key, st, name, S, m, _ = best
     avg_ms = st["total_ms"] / st["launches"]
-    byt = kernel_bytes(name, n, nnz, m, S, (mats or {}).get(S))
+    byt = kernel_bytes(name, n, nnz, m, S, (mats or {}).get((name, S)))
     achieved = byt / (avg_ms * 1e-3) / 1e9 if byt else None
     return {"kernel": key, "class": "/".join(key.split("/")[:3]), "launches": st["seen"], "timed": st["launches"],
             "avg_us": avg_ms * 1e3, "bytes_per_launch": byt, "achieved": achieved}
@@ -314,7 +317,7 @@ def gspmv_sweep(torch, A, ms, dtypes, flush=False, reps=50, plain=False):
             for tag, between in runs.items():
                 us = event_times_us(torch, lambda: M.gspmv(X, out=Y), reps, 5, between)
                 med = float(np.median(us))
-                byt = M.stream_bytes(dt) + 2 * S * m * A.n
+                byt = M.product_bytes(m, dt) + 2 * S * m * A.n
                 gbs = byt / (med * 1e-6) / 1e9
                 rec[tag] = {"us_median": round(med, 2), "us_p10": round(float(np.percentile(us, 10)), 2),
                             "us_p90": round(float(np.percentile(us, 90)), 2), "GBps": round(gbs, 1),
@@ -781,7 +784,7 @@ def summarize_profiles(out, workload, m):
             cls = kernel_class(r["Name"])
             parts = cls.split("/")
             byt = kernel_bytes(parts[0], A.n, A.nnz, int(parts[2][1:]), 8 if parts[1] == "f64" else 4,
-                               summary_mat(A, parts[0], 8 if parts[1] == "f64" else 4)) \
+                               summary_mat(A, parts[0], 8 if parts[1] == "f64" else 4, r["Name"])) \
                 if len(parts) == 3 else None
             avg = float(r["AverageNs"]) / 1e3
             lines.append(f"| {cls} | {r['Calls']} | {avg:.1f} | {float(r['MinNs']) / 1e3:.1f} | "
@@ -794,9 +797,10 @@ def summarize_profiles(out, workload, m):
                 if "copyBuffer" in r["Kernel_Name"]]
         if vals:
             cal[c] = (1 << 20) / (sum(vals) / len(vals))   # 1 GiB = 1048576 KiB
-    per = {}
+    per, symbol = {}, {}
     for c, sub in (("FETCH_SIZE", "fetch"), ("WRITE_SIZE", "write")):
         for r in rows(sub, "counter_collection.csv"):
+            symbol[kernel_class(r["Kernel_Name"])] = r["Kernel_Name"]
             per.setdefault(kernel_class(r["Kernel_Name"]), {}).setdefault(c, []).append(float(r["Counter_Value"]))
     traffic = []
     if per and len(cal) == 2:
@@ -812,7 +816,7 @@ def summarize_profiles(out, workload, m):
             hbm = (f * cal["FETCH_SIZE"] + w * cal["WRITE_SIZE"]) * 1024
             name, dt, mt = cls.split("/")
             S = 8 if dt == "f64" else 4
-            byt = kernel_bytes(name, A.n, A.nnz, int(mt[1:]), S, summary_mat(A, name, S))
+            byt = kernel_bytes(name, A.n, A.nnz, int(mt[1:]), S, summary_mat(A, name, S, symbol[cls]))
             ratio = f"{hbm / byt:.3f}" if byt else ""
             lines.append(f"| {cls} | {len(d['FETCH_SIZE'])} | {f:.0f} | {w:.0f} | {hbm / 1e6:.1f} | "
                          f"{byt / 1e6 if byt else '':{'.1f' if byt else ''}} | {ratio} |")
@@ -1007,8 +1011,9 @@ def main():
     if args.warmup:
         timed_solves(torch, M, B, X, ws, args.warmup, label="warm-up")
     step_s, infos, trace = timed_solves(torch, M, B, X, ws, args.steps, trace=True, label="timed")
-    mats = {8: M.stream_bytes("f64", True), 4: M.stream_bytes("f32", True)}
-    log(f"matrix bytes per product: binary64 {mats[8]}, binary32 {mats[4]}")
+    mats = {(name, S): M.product_bytes(m, "f64" if S == 8 else "f32", name)
+            for name in ("gspmv", "spmv_sigma", "spmv_omega") for S in (8, 4)}
+    log(f"matrix bytes per product: {mats}")
     dom = dominant_kernel(trace, A.n, A.nnz, mats)
     iters = max(i["iters"] for i in infos)
     log(f"step {step_s * 1e3:.2f} ms, {iters} iterations, dominant {dom['kernel']} {dom['avg_us']:.1f} us")

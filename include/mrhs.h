@@ -126,7 +126,7 @@ const char *mrhs_version(void);
  * average, 16,384 rows and more), the products that gain from it read one
  * 2-byte pattern number per row and a table of patterns instead
  * (MRHS_CSR_PATTERN=0: none); results are the same bit for bit.  See
- * csr_stream_bytes.
+ * csr_stream_bytes and csr_product_bytes.
  */
 mrhs_status csr_create(int32_t n, int64_t nnz, const int32_t *row_ptr,
                        const int32_t *col_idx, const double *val,
@@ -155,12 +155,26 @@ mrhs_status csr_info(mrhs_csr A, int32_t *n, int64_t *nnz, size_t *device_bytes)
  * Bytes one tiled product streams from the matrix arrays (Section 2.3: the
  * matrix part of the GSpMV memory traffic), row patterns left aside: the row
  * offsets plus, per entry, a 2- or 4-byte code in the dictionary form or a
- * 4-byte column index and a value otherwise.  dtype MRHS_F64 or MRHS_F32; scaled != 0 for the solvers'
- * column-scaled matrix A D^-1, 0 for A.  gspmv of a handle made with
- * MRHS_CSR_REORDER reads the caller's arrays in plain form.  EINVAL: NULL
- * handle or output, unknown dtype.
+ * 4-byte column index and a value otherwise.  dtype MRHS_F64 or MRHS_F32;
+ * scaled != 0 for the solvers' column-scaled matrix A D^-1, 0 for A.  gspmv of
+ * a handle made with MRHS_CSR_REORDER reads the caller's arrays in plain form.
+ * EINVAL: NULL handle or output, unknown dtype.
  */
 mrhs_status csr_stream_bytes(mrhs_csr A, int32_t dtype, int32_t scaled, int64_t *bytes);
+
+/* Products of a block of m vectors: Y = A X, and the two of an iteration. */
+#define MRHS_PRODUCT_GSPMV 0
+#define MRHS_PRODUCT_SIGMA 1
+#define MRHS_PRODUCT_OMEGA 2
+
+/*
+ * Bytes that product of block width m reads from the matrix arrays in the form
+ * it takes: row patterns (2 bytes per row and the pattern table) where it reads
+ * them, else what csr_stream_bytes reports (gspmv of a handle made with
+ * MRHS_CSR_REORDER: the caller's plain arrays).  EINVAL: NULL handle or output,
+ * unknown dtype or product, m outside [1, 16].
+ */
+mrhs_status csr_product_bytes(mrhs_csr A, int32_t dtype, int32_t m, int32_t product, int64_t *bytes);
 
 /*
  * Y = A X (Section 2.3, Figure 1) for device blocks X, Y of m binary64

@@ -27,6 +27,7 @@ NOALLOC_SCRATCH_BYTES = 64 << 20  # MRHS_NOALLOC_SCRATCH_BYTES
 # every symbol include/mrhs.h declares
 EXPORTS = (
     "mrhs_last_error", "mrhs_version", "csr_create", "csr_destroy", "csr_info", "csr_stream_bytes",
+    "csr_product_bytes",
     "csr_reorder_permutation",
     "gspmv", "gspmv_ex",
     "block_bicgstab", "block_bicgstab_ex", "block_bicgstab_workspace_size", "block_bicgstab_noalloc",
@@ -37,6 +38,7 @@ EXPORTS = (
     "amg_create", "amg_destroy", "amg_info", "amg_level", "amg_level_copy", "amg_vcycle_workspace_size",
     "amg_vcycle", "block_bicgstab_amg_workspace_size", "block_bicgstab_amg",
 )
+PRODUCTS = {"gspmv": 0, "spmv_sigma": 1, "spmv_omega": 2}
 AMG_OPERATOR, AMG_PROLONGATION, AMG_SPLIT = 0, 1, 2
 PROBE_KINDS = {"read": 0, "read_nt": 1, "write": 2, "write_nt": 3, "copy": 4, "copy_nt": 5}
 
@@ -80,6 +82,7 @@ def _declare(lib):
         "csr_destroy": [vp],
         "csr_info": [vp, c.POINTER(i32), c.POINTER(i64), c.POINTER(sz)],
         "csr_stream_bytes": [vp, i32, i32, c.POINTER(i64)],
+        "csr_product_bytes": [vp, i32, i32, i32, c.POINTER(i64)],
         "csr_reorder_permutation": [i32, vp, vp, vp],
         "gspmv": [vp, vp, vp, i32],
         "gspmv_ex": [vp, i32, vp, vp, i32, vp],

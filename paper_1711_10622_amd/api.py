@@ -84,6 +84,14 @@ class CsrMatrix:
         _lib.check(self._lib.csr_stream_bytes(self._h, dt, 1 if scaled else 0, ctypes.byref(b)))
         return int(b.value)
 
+    def product_bytes(self, m, dtype="f64", product="gspmv") -> int:
+        """Bytes that product ("gspmv", "spmv_sigma" or "spmv_omega") of block
+        width m reads from the matrix arrays, row patterns where it reads them."""
+        b = ctypes.c_int64()
+        dt = _lib.F64 if dtype == "f64" else _lib.F32
+        _lib.check(self._lib.csr_product_bytes(self._h, dt, m, _lib.PRODUCTS[product], ctypes.byref(b)))
+        return int(b.value)
+
     def close(self):
         if getattr(self, "_h", None) is not None and self._h.value:
             self._lib.csr_destroy(self._h)

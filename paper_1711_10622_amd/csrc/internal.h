@@ -51,7 +51,7 @@ struct mrhs_csr_s {
     // arrays 0 and 2, past kPatRows rows of all four
     uint16_t *pid = nullptr;
     int32_t *plen = nullptr;
-    int32_t pk = 0;
+    int32_t pk = 0, npat = 0;
     void *pent[4] = {nullptr, nullptr, nullptr, nullptr};
     void *pst[4] = {nullptr, nullptr, nullptr, nullptr};  // of arrays 1 and 3
 };

@@ -364,6 +364,7 @@ mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, cons
                  (st = pattern_arrays(A, p, dict::pattern_table(p, rp, ci, h.data()), 1, true, total))))
                 return st;
             A->pk = p.pk;
+            A->npat = static_cast<int32_t>(p.rep.size());
             if ((st = upload_vec(&A->pid, p.id, total)))
                 return st;
         }
@@ -423,6 +424,20 @@ struct StoreLaunch {
         return launch_gspmv<T, M>(user_view<T>(*A),
                                   OpStore<T, M>{static_cast<const T *>(X), static_cast<T *>(Y)},
                                   RedBufs<T>{nullptr, nullptr, nullptr}, s);
+    }
+};
+
+// Whether a product of MRHS_PRODUCT_* reads the row patterns of a matrix that
+// has them.
+template <typename T>
+struct ReadsPatterns {
+    int32_t n, product;
+    template <int M>
+    bool operator()() const
+    {
+        return product == MRHS_PRODUCT_GSPMV   ? pattern_pays<T, M, OpStore<T, M>>(n)
+               : product == MRHS_PRODUCT_SIGMA ? pattern_pays<T, M, OpSpmv1<T, M>>(n)
+                                               : pattern_pays<T, M, OpSpmv2<T, M>>(n);
     }
 };
 
@@ -654,6 +669,34 @@ MRHS_API mrhs_status csr_stream_bytes(mrhs_csr A, int32_t dtype, int32_t scaled,
     const int64_t per = A->code[k] ? 2 : A->ccode[k] ? 4 : 4 + (dtype == MRHS_F64 ? 8 : 4);
     *bytes = 4 * (static_cast<int64_t>(A->n) + 1) + per * A->nnz;
     return MRHS_OK;
+}
+
+MRHS_API mrhs_status csr_product_bytes(mrhs_csr A, int32_t dtype, int32_t m, int32_t product, int64_t *bytes)
+{
+    clear_error();
+    if (!A || !bytes)
+        return set_error(MRHS_EINVAL, "NULL argument");
+    if (m < 1 || m > kMaxM)
+        return set_error(MRHS_EINVAL, "m = %d outside [1, 16]", m);
+    if (dtype != MRHS_F64 && dtype != MRHS_F32)
+        return set_error(MRHS_EINVAL, "unknown dtype %d", dtype);
+    if (product < MRHS_PRODUCT_GSPMV || product > MRHS_PRODUCT_OMEGA)
+        return set_error(MRHS_EINVAL, "unknown product %d", product);
+    const bool f64 = dtype == MRHS_F64;
+    if (product == MRHS_PRODUCT_GSPMV && A->perm) {
+        *bytes = 4 * (static_cast<int64_t>(A->n) + 1) + (f64 ? 12 : 8) * A->nnz;
+        return MRHS_OK;
+    }
+    const int k = (f64 ? 0 : 2) + (product == MRHS_PRODUCT_GSPMV ? 0 : 1);
+    if (A->pent[k] && (f64 ? dispatch_m(m, ReadsPatterns<double>{A->n, product})
+                           : dispatch_m(m, ReadsPatterns<float>{A->n, product}))) {
+        int64_t row = sizeof(int32_t) + static_cast<int64_t>(A->pk) * (f64 ? sizeof(PatEntry<double>) : sizeof(PatEntry<float>));
+        if (product == MRHS_PRODUCT_OMEGA)
+            row += f64 ? sizeof(PatStencil<double>) : sizeof(PatStencil<float>);
+        *bytes = 2 * static_cast<int64_t>(A->n) + row * A->npat;
+        return MRHS_OK;
+    }
+    return csr_stream_bytes(A, dtype, product == MRHS_PRODUCT_GSPMV ? 0 : 1, bytes);
 }
 
 MRHS_API mrhs_status gspmv_ex(mrhs_csr A, int32_t dtype, const void *X, void *Y, int32_t m, void *hip_stream)
