@@ -26,3 +26,14 @@ def test_dominant_kernel_takes_its_own_matrix_bytes():
              "xr_update/f64/m16/g512": {"launches": 4, "seen": 4, "total_ms": 1.0}}
     d = bench.dominant_kernel(trace, n, nnz, {("spmv_sigma", 8): 16800, ("spmv_omega", 8): 2000})
     assert d["bytes_per_launch"] == 2000 + 3 * 8 * m * n
+
+
+def test_every_kernel_has_a_name():
+    for symbol, cls in (
+            ("void mrhs::k_cols<mrhs::OpColDots>(mrhs::ColBatch, int)", "gcr_dots/f64/m1"),
+            ("void mrhs::k_cols<mrhs::OpColUpdate>(mrhs::ColBatch, int)", "gcr_update/f64/m1"),
+            ("void mrhs::k_gspmv_split<float, 8, mrhs::OpVcRes<float, 8> >(mrhs::CsrView<float>, int)", "vc_resid/f32/m8"),
+            ("void mrhs::k_stream<double, 16, mrhs::OpXR<double, 16> >(int)", "xr_update/f64/m16"),
+            ("void mrhs::k_gspmv_march<double, 8, mrhs::OpStore<double, 8> >(int)", "gspmv/f64/m8")):
+        assert bench.kernel_class(symbol) == cls
+    assert bench.kernel_class("mrhs::k_ctl_reset(mrhs::Ctl*)") == "mrhs::k_ctl_reset"
