@@ -33,7 +33,8 @@ m = 1, 2, 4, 8, 16 with the speedup per right-hand side beside the paper's
 traffic models (Section 2.3), the generalized SpMV sweep m = 1..16 (binary64
 and binary32), the 524k-row channel (solves per m, mixed, error against the
 oracle), the relabelled cube channel (m = 8) in both precisions, the ensemble
-projection step, and open-loop serving (p50/p99 latency, RHS/s).
+projection step, and open-loop serving (p50/p99 latency, RHS/s).  The line holds
+these in short form; --details FILE writes them in full.
 """
 from __future__ import annotations
 
@@ -57,6 +58,44 @@ HBM_PEAK_GBS = 8000.0
 TRACE_EVERY = 8
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_solve_chan256_m16.md")
 HEADLINE = "chan256"
+
+
+# A reader that keeps the last 8000 characters of standard output must still
+# find the whole line in them.
+LINE_CHARS = 7500
+# legs' details that only --details holds
+DETAILS = {"kernels", "top_kernels", "us_p10", "us_p90", "frac_hbm_peak", "iters", "outer", "rows_per_level",
+           "rel_diff_vs_fp64_solution", "paper_compact_5m_2m3", "paper_full_C", "compulsory_bytes_model",
+           "max_outstanding", "server_rhs_per_s", "offered_rhs_per_s", "wall_s", "timed", "seen"}
+
+
+def shorten(v):
+    """A leg's results without their details: [us, GB/s] for a timed product,
+    five significant digits for a number."""
+    if isinstance(v, dict):
+        if "us_median" in v and "GBps" in v:
+            return [shorten(v["us_median"]), shorten(v["GBps"])]
+        return {k: shorten(x) for k, x in v.items() if k not in DETAILS}
+    if isinstance(v, (list, tuple)):
+        return [shorten(x) for x in v]
+    if isinstance(v, float):
+        return float(f"{v:.5g}")
+    return v
+
+
+def result_line(result, extra):
+    """The one line of standard output: ``result`` and the legs in short form,
+    at most LINE_CHARS characters; legs that do not fit are named in
+    ``left_out``, the largest first."""
+    legs = shorten(extra)
+    left = []
+    while True:
+        out = dict(result, extra=dict(legs, left_out=left) if left else legs)
+        line = json.dumps(out)
+        if len(line) <= LINE_CHARS or not legs:
+            return line
+        left.append(max(legs, key=lambda k: len(json.dumps(legs[k]))))
+        del legs[left[-1]]
 
 
 def log(msg):
@@ -867,7 +906,8 @@ def amg_legs(torch, A, Bh, m, t_jacobi, per_iter_ms=(1, 2, 4, 8, 16), steps=1, r
     mrhs.trace_enable(False)
     assert st == 0, infos
     out.update({"m": m, "s_per_rhs": round(t / m, 6), "speedup_vs_jacobi": round(t_jacobi / t, 3),
-                "iters": [i["iters"] for i in infos], "max_relres": max(i["relres"] for i in infos),
+                "iters": [i["iters"] for i in infos], "iters_max": max(i["iters"] for i in infos),
+                "max_relres": max(i["relres"] for i in infos),
                 "top_kernels": {k: {"launches": v["seen"], "avg_us": round(v["total_ms"] / v["launches"] * 1e3, 1)}
                                 for k, v in sorted(tr.items(), key=lambda kv: -kv[1]["total_ms"] / kv[1]["launches"]
                                                    * kv[1]["seen"])[:8]}})
@@ -968,6 +1008,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=1)
     ap.add_argument("--quick", action="store_true", help="only the timed solve (for profiling)")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle legs")
+    ap.add_argument("--details", metavar="FILE", help="write every leg's full results to FILE as JSON")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="run only a plain 1 GiB copy (counter calibration under rocprofv3)")
     ap.add_argument("--solve-only", metavar="WORKLOAD",
@@ -1023,7 +1064,10 @@ def main():
     dom = dominant_kernel(trace, A.n, A.nnz, mats)
     iters = max(i["iters"] for i in infos)
     log(f"step {step_s * 1e3:.2f} ms, {iters} iterations, dominant {dom['kernel']} {dom['avg_us']:.1f} us")
-    extra = {"iters": [i["iters"] for i in infos], "max_relres": max(i["relres"] for i in infos),
+    extra = {"iters": [i["iters"] for i in infos], "iters_max": iters, "max_relres": max(i["relres"] for i in infos),
+             "kernels_us": {k: round(v["total_ms"] / v["launches"] * 1e3, 1)
+                            for k, v in sorted(trace.items(), key=lambda kv: -kv[1]["total_ms"] / kv[1]["launches"]
+                                               * kv[1]["seen"])[:4]},
              "kernels": {k: {"launches": v["seen"], "timed": v["launches"],
                              "avg_us": round(v["total_ms"] / v["launches"] * 1e3, 2)}
                          for k, v in trace.items()}}
@@ -1054,6 +1098,7 @@ def main():
         xf = Xf.cpu().numpy()
         extra["mixed"] = {"s_per_rhs": tmix / m, "speedup_vs_fp64": round(step_s / tmix, 3),
                           "iters": [i["iters"] for i in imix], "outer": [i["outer"] for i in imix],
+                          "iters_max": max(i["iters"] for i in imix), "outer_max": max(i["outer"] for i in imix),
                           "max_relres": max(i["relres"] for i in imix),
                           "rel_diff_vs_fp64_solution": [float(np.linalg.norm(d[:, l]) / np.linalg.norm(xf[:, l]))
                                                         for l in range(m)],
@@ -1103,8 +1148,10 @@ def main():
     if not args.no_cpu:
         result["cpu_baseline"] = cpu_baseline(A, Bh, iters, min(host_cores(), m))
         result["cpu_baseline"]["host"] = host_info()
-    result["extra"] = extra
-    print(json.dumps(result), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(dict(result, extra=extra), f, indent=1, default=float)
+    print(result_line(result, extra), flush=True)
     return 0
 
 

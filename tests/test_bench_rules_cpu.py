@@ -1,5 +1,7 @@
 """The benchmark's offline accounting, without a device: which kernels a trace
 names and how many matrix bytes it credits them with."""
+import json
+
 import bench
 from workloads import grids
 
@@ -37,3 +39,37 @@ def test_every_kernel_has_a_name():
             ("void mrhs::k_gspmv_march<double, 8, mrhs::OpStore<double, 8> >(int)", "gspmv/f64/m8")):
         assert bench.kernel_class(symbol) == cls
     assert bench.kernel_class("mrhs::k_ctl_reset(mrhs::Ctl*)") == "mrhs::k_ctl_reset"
+
+
+RESULT = {"metric": bench.METRIC, "value": 0.6345, "unit": "s/RHS", "n_gpus": 1, "steps": 20, "warmup": 5,
+          "ms_per_step": 10151.2, "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "f64",
+          "data": "synthetic", "config": {"workload": "w" * 300, "n": 12582912, "m": 16},
+          "cpu_baseline": {"value": 33.1, "sample": "s" * 400}}
+
+
+def sweep(ms):
+    return {f"{dt}/m{m}": {"us_median": 123.456789, "us_p10": 120.1, "us_p90": 130.2, "GBps": 4321.987,
+                           "frac_hbm_peak": 0.5402} for dt in ("f64", "f32") for m in ms}
+
+
+def test_line_can_be_read_whole():
+    """All legs of a full run: one line that a reader of the last 8000
+    characters still finds, with the result's own fields as they were."""
+    extra = {"iters": list(range(1000, 1016)), "iters_max": 1974, "gspmv_chan256": sweep(range(1, 17)),
+             "gspmv_cube192": {"relabelled": sweep((8, 16)), "rcm": sweep((8, 16))},
+             "amg": {"iters": [14] * 16, "s_per_rhs": 0.123456789, "top_kernels": {f"k{k}": {"avg_us": 1.0} for k in
+                                                                                 range(40)}},
+             "serving": {f"leg{k}": {"p50_ms": 22.9, "p99_ms": 96.91, "wall_s": 1.0, "not_ok": 0} for k in range(5)}}
+    line = bench.result_line(RESULT, extra)
+    assert "\n" not in line and len(line) <= bench.LINE_CHARS < 8000
+    out = json.loads(line)
+    assert {k: out[k] for k in RESULT} == RESULT
+    assert out["extra"]["gspmv_chan256"]["f64/m3"] == [123.46, 4322.0]
+    assert out["extra"]["amg"] == {"s_per_rhs": 0.12346} and "left_out" not in out["extra"]
+
+
+def test_legs_that_do_not_fit_are_named():
+    extra = {"iters_max": 5, "large": {str(k): 0.1 for k in range(5000)}, "small": {"a": 1}}
+    out = json.loads(bench.result_line(RESULT, extra))
+    assert out["extra"] == {"iters_max": 5, "small": {"a": 1}, "left_out": ["large"]}
+    assert out["value"] == RESULT["value"]
