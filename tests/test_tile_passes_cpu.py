@@ -1,0 +1,36 @@
+"""Where a full tile is one pass of the workgroup the compiler must know it: the
+passes per tile are then a constant expression whatever the launch says (a
+run-time loop made products of one binary64 column up to 70 % slower on
+multigrid levels), and elsewhere the launch's own count."""
+import subprocess
+
+import pytest
+
+from paper_1711_10622_amd import build
+
+SOURCE = """
+#include "core.h"
+using S = mrhs::Shape<%s, %d>;
+constexpr mrhs::TilePlan launch{2, 1};
+static_assert(S::PASSES %s 1, "");
+static_assert(mrhs::plan_passes<S>(launch) == %d, "passes of the tile");
+"""
+
+
+@pytest.mark.parametrize("t,m", [("double", 1), ("double", 2), ("float", 1), ("float", 2), ("float", 4)])
+def test_one_pass_is_a_constant(tmp_path, t, m):
+    assert compiles(tmp_path, SOURCE % (t, m, "==", 1))
+
+
+@pytest.mark.parametrize("t,m", [("double", 4), ("double", 9), ("double", 16), ("float", 8), ("float", 16)])
+def test_other_tiles_follow_the_launch(tmp_path, t, m):
+    assert compiles(tmp_path, SOURCE % (t, m, ">", 2))
+
+
+def compiles(tmp_path, text):
+    src = tmp_path / "probe.hip"
+    src.write_text(text)
+    r = subprocess.run([build.hipcc(), *build.flags(), "--cuda-host-only", "-fsyntax-only", str(src)],
+                       capture_output=True, text=True)
+    assert "fatal" not in r.stderr
+    return r.returncode == 0 or pytest.fail(r.stderr[-1500:])
