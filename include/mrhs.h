@@ -125,8 +125,8 @@ const char *mrhs_version(void);
  * rows of 16-bit codes repeat (at most 4096 different ones, eight rows each on
  * average, 16,384 rows and more), the products that gain from it read one
  * 2-byte pattern number per row and a table of patterns instead
- * (MRHS_CSR_PATTERN=0: none); results are the same bit for bit.  See
- * csr_stream_bytes and csr_product_bytes.
+ * (MRHS_CSR_PATTERN=0: none, 2: also products that do not gain); results are
+ * the same bit for bit.  See csr_stream_bytes and csr_product_bytes.
  */
 mrhs_status csr_create(int32_t n, int64_t nnz, const int32_t *row_ptr,
                        const int32_t *col_idx, const double *val,

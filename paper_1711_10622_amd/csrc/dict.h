@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <numeric>
 #include <thread>
 #include <vector>
 
@@ -209,6 +210,7 @@ Codes<V> codes(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *ci, con
 struct Patterns {
     bool ok = false;
     int32_t pk = 0;               // entries per pattern in the table (whole batches)
+    int32_t run = 0;              // mean run of rows with one pattern
     std::vector<uint16_t> id;     // [n]
     std::vector<int32_t> rep;     // a row of each pattern
     std::vector<int32_t> len;     // its entries
@@ -297,10 +299,16 @@ inline Patterns patterns(int32_t n, const int32_t *rp, const uint16_t *c0, const
     const int64_t npat = static_cast<int64_t>(all.rows.size());
     if (npat * kPatRowsPer > n || npat * out.pk > kPatEntries)
         return out;
+    std::vector<int32_t> runs(T, 0);
     row_ranges(n, T, [&](int32_t lo, int32_t hi, int t) {
-        for (int32_t i = lo; i < hi; ++i)
+        int32_t count = 0;
+        for (int32_t i = lo; i < hi; ++i) {
             out.id[i] = map[t][out.id[i]];
+            count += i == lo || out.id[i] != out.id[i - 1];
+        }
+        runs[t] = count;
     });
+    out.run = static_cast<int32_t>(n / std::max<int64_t>(1, std::accumulate(runs.begin(), runs.end(), int64_t{0})));
     out.rep = all.rows;
     out.ok = true;
     return out;

@@ -51,7 +51,7 @@ struct mrhs_csr_s {
     // arrays 0 and 2, past kPatRows rows of all four
     uint16_t *pid = nullptr;
     int32_t *plen = nullptr;
-    int32_t pk = 0, npat = 0;
+    int32_t pk = 0, npat = 0, prun = 0;
     void *pent[4] = {nullptr, nullptr, nullptr, nullptr};
     void *pst[4] = {nullptr, nullptr, nullptr, nullptr};  // of arrays 1 and 3
 };
@@ -91,6 +91,7 @@ inline CsrView<T> view_of(const mrhs_csr_s &A, const T *va, int k)
         v.pst = static_cast<const PatStencil<T> *>(A.pst[k]);
         v.plen = A.plen;
         v.pk = A.pk;
+        v.prun = A.prun;
     }
     if (A.code[k]) {
         v.code = A.code[k];
@@ -265,61 +266,73 @@ inline int split_slots(int32_t avg, int row_slots)
     return slots;
 }
 
-// Whether a product over n rows reads the row patterns of a matrix that has
-// them (else its codes).  Measured, codes -> patterns:
-//  * plain products (no reduction) from pattern_min_rows to kPatRows rows, and
-//    of narrow rows above: 938k-row channel (131x77x93) m = 1 25.5 -> 23.1 us,
-//    m = 4 35.5 -> 29.5, m = 7 54 -> 48, m = 8 48 -> 40, binary32 m = 16 45 ->
-//    39; 2.08M rows m = 8 87 -> 68, m = 16 157 -> 147; 12.6M-row channel m = 1
-//    139 -> 105, m = 2 181 -> 118.  Wider rows of larger matrices wait for
-//    block rows, not for the matrix: on the 12.6M-row channel they gain nothing
-//    from waves that run further apart (m = 4 317 -> 306, m = 7 661 -> 725, m =
-//    8 525 -> 533); between 2.1 and 6.3M rows only the codes were measured;
-//  * two blocks gathered per entry past kPatRows: spmv_omega on the 12.6M-row
-//    channel m = 4 500 -> 448 us, m = 8 928 -> 849, m = 16 1790 -> 1651; on the
-//    524k-row one it is no faster (m = 4 28.0 -> 29.7, m = 16 79.2 -> 81.4);
+// Whether a product reads the row patterns of a matrix that has them (else its
+// codes).  Where all rows of a wave have one pattern its entries come through
+// scalar loads; a wave with several (at the ends of grid lines) gathers four
+// entries at a time through vector loads of the table.  So what decides is how
+// many rows in a row share a pattern (CsrView::prun: a third of the grid line)
+// against the rows and bytes of a wave.  Measured, codes / patterns, lines of
+// 13 / 28 / 40 / 56 / 80 / 130 rows:
+//  * plain products, 400,000 rows: m = 1 .95 / .96 / .97 / .97 / .97 / 1.07, m =
+//    4 .93 / .93 / .95 / .99 / 1.01 / 1.09, m = 16 .87 / .95 / .97 / 1.00 / 1.04
+//    / 1.07, binary32 m = 8 1.02 / 1.03 / 1.01 / 1.06 / 1.05 / 1.07, m = 16 .95 /
+//    1.02 / 1.02 / 1.04 / 1.06 / 1.05; 1.6M rows: m = 1 .92 / .97 / 1.00 / 1.03
+//    / 1.02 / 1.17, m = 4 .89 / .92 / .95 / 1.05 / 1.11 / 1.26, m = 16 .92 / 1.02
+//    / 1.04 / 1.11 / 1.07 / 1.00, binary32 m = 7 .70 / .91 / .95 / 1.03 / 1.03 /
+//    1.10.  One-element 8-byte lanes lose longer: m = 5 .67 / .82 / .91 / .94 /
+//    1.04 / 1.10, m = 11 .78 / .88 / .79 / 1.00 / .93 / 1.04, and with four rows
+//    to a wave (m = 13 and 15) at every line (128 rows 1.01, 96 rows .91);
+//  * of more than kPatRows rows only narrow rows: 12.6M-row channel (lines of
+//    256) m = 1 139 -> 105 us, m = 2 181 -> 118.  Wider rows there wait for block
+//    rows, not for the matrix, and gain nothing from waves that run further
+//    apart (m = 4 317 -> 306, m = 7 661 -> 725, m = 8 525 -> 533); between 2.1
+//    and 6.3M rows only their codes were measured;
+//  * two blocks gathered per entry past kPatRows, 2.2M rows: m = 1 .97 / 1.00 /
+//    1.03 / 1.03 / 1.01 / 1.12, m = 4 .91 / .92 / .92 / 1.01 / 1.04 / 1.13, m = 16
+//    .85 / 1.00 / 1.03 / 1.08 / 1.09 / 1.09, binary32 m = 4 1.11 / 1.14 / 1.16 /
+//    1.16 / 1.16 / 1.29, m = 8 .90 / .92 / .92 / .98 / 1.01 / 1.06, m = 16 .75 /
+//    .82 / .86 / .93 / .98 / 1.00; spmv_omega on the 12.6M-row channel m = 16
+//    1790 -> 1640 us; on the 524k-row one it is no faster (m = 4 28.0 -> 29.7, m
+//    = 16 79.2 -> 81.4);
 //  * the others never: spmv_sigma on the 524k-row channel m = 4 20.5 -> 22.9,
 //    32^3 m = 16 11.0 -> 11.6, xr_sigma m = 4 51 -> 55.
 //
-// Rows of a plain product from which patterns pay.  A wave whose rows have
-// several patterns (at the ends of grid lines) gathers four entries at a time
-// through vector loads of the table, which costs most where many lanes share a
-// row and on matrices of few waves.  Speedup over codes (captured graphs of 40
-// products) at 20k / 49k / 111k / 184k / 295k / 390k / 524k / 819k rows:
-//  * binary64 rows of one-element lanes, m = 5 .96 / .94 / .94 / .99 / .98 /
-//    1.05 / 1.13 / 1.16, m = 7 .92 / .99 / .98 / .99 / .99 / 1.05 / 1.08 /
-//    1.15, m = 9 .91 / 1.00 / 1.01 / 1.03 / .98 / .97 / 1.02 / 1.03; of 13 and
-//    15 columns, four rows to a wave, m = 13 .99 / .97 / .95 / 1.01 / .91 / 1.00
-//    / 1.01 / .91 and 1.02 at 2.08M: never;
-//  * five lanes to a row, m = 10 1.00 / .97 / .96 / 1.02 / .99 / 1.09 / 1.06 /
-//    1.13, binary32 m = 5 .99 / .98 / .96 / 1.03 / 1.04 / 1.08 / 1.14 / 1.17;
-//  * the others, m = 1 1.04 / 1.00 / 1.01 / .98 / .98 / 1.01 / 1.04 / 1.02, m =
-//    16 1.05 / 1.03 / 1.03 / 1.07 / .97 / 1.07 / 1.08 / 1.02, binary32 m = 11
-//    1.05 / 1.05 / 1.04 / 1.10 / 1.16 / 1.01 / 1.08 / 1.20.
-template <typename T, int M>
-constexpr int32_t pattern_min_rows()
+// The mean run of rows from which patterns pay; INT32_MAX: never.
+template <typename T, int M, class Op>
+constexpr int32_t pattern_min_run()
 {
     using S = Shape<T, M>;
-    if (M > 1 && S::VW == 1 && sizeof(T) == 8)
-        return S::RW == 4 ? INT32_MAX : S::RW < 8 ? 1 << 19 : 5 << 16;
-    return S::L == 5 ? 1 << 17 : kPatMinRows;
+    constexpr bool f64 = sizeof(T) == 8;
+    if (gathered_blocks<Op>::value == 2) {
+        if (S::ROW_BYTES <= 16)
+            return f64 ? 6 : 0;
+        return f64 ? 18 : M <= 8 ? 26 : 40;
+    }
+    if (!f64)
+        return S::RW >= 32 ? 0 : 18;
+    if (M <= 2)
+        return 13;
+    if (S::VW > 1)
+        return 18;
+    return S::RW == 4 ? INT32_MAX : S::RW < 8 ? 40 : 26;
 }
 
 // The part the op and the block width decide: whether there is a kernel.
 template <typename T, int M, class Op>
 constexpr bool has_pattern_kernel()
 {
-    return reads_patterns<Op>::value && (gathered_blocks<Op>::value == 2 || pattern_min_rows<T, M>() < INT32_MAX);
+    return reads_patterns<Op>::value && pattern_min_run<T, M, Op>() < INT32_MAX;
 }
 
+// n: rows; run: mean run of rows with one pattern.
 template <typename T, int M, class Op>
-inline bool pattern_pays(int32_t n)
+inline bool pattern_pays(int32_t n, int32_t run)
 {
-    if (!has_pattern_kernel<T, M, Op>())
+    if (!has_pattern_kernel<T, M, Op>() || run < pattern_min_run<T, M, Op>())
         return false;
     if (gathered_blocks<Op>::value == 2)
         return n > kPatRows;
-    return n >= pattern_min_rows<T, M>() && (n <= kPatRows || Shape<T, M>::ROW_BYTES <= 16);
+    return n <= kPatRows || Shape<T, M>::ROW_BYTES <= 16;
 }
 
 template <typename T, int M, class Op>
@@ -357,7 +370,7 @@ inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<
     auto *kernel = &k_gspmv<T, M, Op>;
     int most = max_per_cu<Op>::value;
     if constexpr (has_pattern_kernel<T, M, Op>()) {
-        if (A.pid && pattern_pays<T, M, Op>(A.n)) {
+        if (A.pid && pattern_pays<T, M, Op>(A.n, A.prun)) {
             kernel = &k_gspmv_pat<T, M, Op>;
             // a product with a reduction runs on the staged kernel's grid in
             // every form, so that partial dot products do not depend on the

@@ -337,8 +337,9 @@ mrhs_status pattern_arrays(mrhs_csr_s *A, const dict::Patterns &p, const std::ve
 // column offsets, else 32-bit column codes.  Where the coded rows repeat
 // (dict::patterns) there is the row-pattern form too; the binary32
 // arrays are roundings of the binary64 ones, so rows equal in those are equal
-// in these.  MRHS_CSR_DICT=0 turns all forms off, MRHS_CSR_PATTERN=0 the
-// row-pattern form.
+// in these.  MRHS_CSR_DICT=0 turns all forms off; MRHS_CSR_PATTERN: 0 no
+// row-pattern form, 1 (default) read where that is faster, 2 wherever the size
+// allows.
 mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, const double *sval, size_t &total)
 {
     if (!env_int("MRHS_CSR_DICT", 1, 0, 1) || A->nnz == 0)
@@ -353,7 +354,8 @@ mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, cons
         return set_error(MRHS_EDEVICE, "read-back failed: %s", hipGetErrorString(e));
     const dict::Codes<double> c0 = dict::codes<double>(A->n, A->nnz, rp, ci, sval, offs);
     const dict::Codes<double> c1 = dict::codes<double>(A->n, A->nnz, rp, ci, h.data(), offs);
-    if (offs.ok && c0.ok && c1.ok && pattern_rows(A->n) && env_int("MRHS_CSR_PATTERN", 1, 0, 1)) {
+    const int mode = env_int("MRHS_CSR_PATTERN", 1, 0, 2);
+    if (offs.ok && c0.ok && c1.ok && pattern_rows(A->n) && mode) {
         const dict::Patterns p = dict::patterns(A->n, rp, c0.code.data(), c1.code.data());
         if (p.ok) {
             // plain products read A's patterns, the omega pass past kPatRows
@@ -365,6 +367,7 @@ mrhs_status build_dict(mrhs_csr_s *A, const int32_t *rp, const int32_t *ci, cons
                 return st;
             A->pk = p.pk;
             A->npat = static_cast<int32_t>(p.rep.size());
+            A->prun = mode == 2 ? INT32_MAX : p.run;
             if ((st = upload_vec(&A->pid, p.id, total)))
                 return st;
         }
@@ -431,13 +434,13 @@ struct StoreLaunch {
 // has them.
 template <typename T>
 struct ReadsPatterns {
-    int32_t n, product;
+    int32_t n, run, product;
     template <int M>
     bool operator()() const
     {
-        return product == MRHS_PRODUCT_GSPMV   ? pattern_pays<T, M, OpStore<T, M>>(n)
-               : product == MRHS_PRODUCT_SIGMA ? pattern_pays<T, M, OpSpmv1<T, M>>(n)
-                                               : pattern_pays<T, M, OpSpmv2<T, M>>(n);
+        return product == MRHS_PRODUCT_GSPMV   ? pattern_pays<T, M, OpStore<T, M>>(n, run)
+               : product == MRHS_PRODUCT_SIGMA ? pattern_pays<T, M, OpSpmv1<T, M>>(n, run)
+                                               : pattern_pays<T, M, OpSpmv2<T, M>>(n, run);
     }
 };
 
@@ -688,9 +691,10 @@ MRHS_API mrhs_status csr_product_bytes(mrhs_csr A, int32_t dtype, int32_t m, int
         return MRHS_OK;
     }
     const int k = (f64 ? 0 : 2) + (product == MRHS_PRODUCT_GSPMV ? 0 : 1);
-    if (A->pent[k] && (f64 ? dispatch_m(m, ReadsPatterns<double>{A->n, product})
-                           : dispatch_m(m, ReadsPatterns<float>{A->n, product}))) {
-        int64_t row = sizeof(int32_t) + static_cast<int64_t>(A->pk) * (f64 ? sizeof(PatEntry<double>) : sizeof(PatEntry<float>));
+    if (A->pent[k] && (f64 ? dispatch_m(m, ReadsPatterns<double>{A->n, A->prun, product})
+                           : dispatch_m(m, ReadsPatterns<float>{A->n, A->prun, product}))) {
+        const size_t entry = f64 ? sizeof(PatEntry<double>) : sizeof(PatEntry<float>);
+        int64_t row = static_cast<int64_t>(sizeof(int32_t) + entry * A->pk);
         if (product == MRHS_PRODUCT_OMEGA)
             row += f64 ? sizeof(PatStencil<double>) : sizeof(PatStencil<float>);
         *bytes = 2 * static_cast<int64_t>(A->n) + row * A->npat;

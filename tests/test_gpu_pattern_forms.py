@@ -1,11 +1,12 @@
 """GPU parity of the row-pattern products at the sizes and widths that run them.
 
 Every matrix here is shown to hold patterns (its handle is larger than the one
-made with MRHS_CSR_PATTERN=0) and has more rows than the dispatch rule asks of
-its block widths; products and solves must give the bits of the coded and plain
-forms.  Past 2^21 rows the omega pass of both precisions reads patterns through
-gspmv_near_pat: waves whose rows are one whole stencil, one partial stencil (at
-a wall), several patterns (line ends) and no stencil at all.
+made with MRHS_CSR_PATTERN=0) and reads them in every product that has a kernel
+for them (MRHS_CSR_PATTERN=2), also where codes would be faster; products and
+solves must give the bits of the coded and plain forms.  Past 2^21 rows the
+omega pass of both precisions reads patterns through gspmv_near_pat: waves whose
+rows are one whole stencil, one partial stencil (at a wall), several patterns
+(line ends) and no stencil at all.
 """
 import os
 
@@ -39,8 +40,14 @@ def make(p, A, **env):
 
 def forms(p, A):
     """The handle under test and the ones it must agree with."""
-    M, F, P = make(p, A), make(p, A, MRHS_CSR_PATTERN="0"), make(p, A, MRHS_CSR_DICT="0")
+    M, F, P = (make(p, A, MRHS_CSR_PATTERN="2"), make(p, A, MRHS_CSR_PATTERN="0"), make(p, A, MRHS_CSR_DICT="0"))
     assert M.device_bytes() > F.device_bytes()  # patterns are there
+    if A.n <= 1 << 21:
+        assert all(M.product_bytes(m, dt) < F.product_bytes(m, dt) for dt in ("f64", "f32") for m in range(1, 17)
+                   if dt == "f32" or m not in (13, 15))
+    else:
+        assert all(M.product_bytes(m, dt, "spmv_omega") < F.product_bytes(m, dt, "spmv_omega")
+                   for dt in ("f64", "f32") for m in range(1, 17))
     return M, F, P
 
 
@@ -61,10 +68,9 @@ def cuda(torch, X):
     return torch.from_numpy(np.ascontiguousarray(X)).cuda()
 
 
-# past 2^19 rows, where plain products of every width that has a kernel read
-# patterns: lines longer and much shorter than a wave's rows, ragged tiles, rows
-# out of the stencil's order with repeated and missing entries, rows of two and
-# a half gather batches
+# lines longer and much shorter than a wave's rows, ragged tiles, rows out of the
+# stencil's order with repeated and missing entries, rows of two and a half
+# gather batches
 CASES = {
     "chan131x67x61": lambda: grids.channel7(131, 67, 61, beta=2.0),
     "dir5x331x331": lambda: grids.dirichlet7(5, 331, 331),
@@ -78,7 +84,6 @@ CASES = {
 def test_products_bitwise(env, name):
     torch, p = env
     A = CASES[name]()
-    assert A.n > 1 << 19
     M, *others = forms(p, A)
     for m in range(1, 17):
         X = rng.rhs_block(A.n, m, 1500 + m)
