@@ -242,16 +242,22 @@ void trace_end(int slot, hipStream_t s);
 // (a 32^3 operator has 128 tiles of 256 rows) and aim at one workgroup per CU,
 // since the reduction's last workgroups read every workgroup's sums: 32^3
 // Dirichlet, m = 16, spmv_sigma 18.1 us on 128 workgroups, 14.8 on 256, 16.5
-// on 512, 21.6 on 1024.  Without a reduction more workgroups do not pay: a
-// plain product on the same block takes 16.5 us on 128 and 19.0 on 256.
+// on 512, 21.6 on 1024.  Rounded up, so that no CU has two tiles: 53,760 rows of
+// the cubes, m = 6, 32 iterations 1.72 ms on 280 workgroups, 1.52 on 210.
+// Without a reduction more workgroups do not pay: a plain product on the same
+// block takes 16.5 us on 128 and 19.0 on 256 (not the dispatch, 0.3 ns a
+// workgroup, nor the kind of store; the cause is not known).
+constexpr int balanced_passes(int64_t n, int cus, int pass_rows, int full)
+{
+    const int64_t rows = static_cast<int64_t>(cus) * pass_rows;
+    return static_cast<int>(std::min<int64_t>(full, std::max<int64_t>(1, (n + rows - 1) / rows)));
+}
+
 template <typename T, int M, class Op>
 inline int tile_passes(int32_t n)
 {
     using S = Shape<T, M>;
-    if constexpr (Op::NDOT == 0)
-        return S::PASSES;
-    const int64_t rows = static_cast<int64_t>(num_cu()) * S::RPP;
-    return static_cast<int>(std::min<int64_t>(S::PASSES, std::max<int64_t>(1, n / rows)));
+    return Op::NDOT == 0 ? S::PASSES : balanced_passes(n, num_cu(), S::RPP, S::PASSES);
 }
 
 // Row slots of a wave that share a row in gspmv_rows_split: as many as leave

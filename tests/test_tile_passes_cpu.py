@@ -34,3 +34,16 @@ def compiles(tmp_path, text):
                        capture_output=True, text=True)
     assert "fatal" not in r.stderr
     return r.returncode == 0 or pytest.fail(r.stderr[-1500:])
+
+
+@pytest.mark.parametrize("n,rows,full,passes", [(1, 32, 8, 1), (8192, 32, 8, 1), (8193, 32, 8, 2), (32768, 32, 8, 4),
+                                                (53760, 64, 4, 4), (53760, 32, 8, 7), (65537, 32, 8, 8),
+                                                (12582912, 32, 8, 8), (2147483647, 256, 1, 1)])
+def test_no_unit_gets_two_tiles(tmp_path, n, rows, full, passes):
+    """A reducing kernel's tiles on 256 compute units: no more tiles than units
+    as long as a full tile allows it."""
+    assert compiles(tmp_path, f"""
+#include "internal.h"
+static_assert(mrhs::balanced_passes({n}, 256, {rows}, {full}) == {passes}, "passes");
+""")
+    assert passes == full or -(-n // (passes * rows)) <= 256
