@@ -325,10 +325,15 @@ struct TilePlan {
 // Passes per tile, a constant where a full tile is one pass (rows of up to 16
 // bytes): a loop over a count known only at run time costs those products up to
 // 70 % (plain-array residual of 2.1M rows of 15 entries, m = 1: 124 us against
-// 89; of 162,000 rows 103 against 61).
-template <class S>
+// 89; of 162,000 rows 103 against 61).  With Op also where it has no reduction
+// and so always full tiles: 1-4 % of a V-cycle at widths whose levels run tiled
+// from the plain arrays (m = 9, 100,000 rows 780 us against 769).
+template <class S, class Op = void>
 __host__ __device__ __forceinline__ constexpr int plan_passes(const TilePlan &p)
 {
+    if constexpr (!std::is_void<Op>::value)
+        if (Op::NDOT == 0)
+            return S::PASSES;
     return S::PASSES == 1 ? 1 : p.passes;
 }
 
@@ -1245,7 +1250,7 @@ __device__ __forceinline__ void gspmv_tiles(const CsrView<T> &A, const Op &op,
                                             Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan)
 {
     using S = Shape<T, M>;
-    const int passes = plan_passes<S>(plan);
+    const int passes = plan_passes<S, Op>(plan);
     const int tr_rows = passes * S::RPP;
     __shared__ int32_t s_rp[S::TR + 1];
     __shared__ __align__(16) unsigned char s_buf[TileLds<T, M>::BYTES];

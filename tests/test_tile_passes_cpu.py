@@ -27,6 +27,17 @@ def test_other_tiles_follow_the_launch(tmp_path, t, m):
     assert compiles(tmp_path, SOURCE % (t, m, ">", 2))
 
 
+@pytest.mark.parametrize("ndot,passes", [(0, "S::PASSES"), (1, "2")])
+def test_products_without_a_reduction_take_full_tiles(tmp_path, ndot, passes):
+    assert compiles(tmp_path, f"""
+#include "core.h"
+using S = mrhs::Shape<double, 9>;
+struct Op {{ static constexpr int NDOT = {ndot}; }};
+constexpr mrhs::TilePlan launch{{2, 1}};
+static_assert(mrhs::plan_passes<S, Op>(launch) == {passes}, "passes of the tile");
+""")
+
+
 def compiles(tmp_path, text):
     src = tmp_path / "probe.hip"
     src.write_text(text)
