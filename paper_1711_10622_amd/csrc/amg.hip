@@ -654,13 +654,18 @@ int32_t median_reach(const amg::HostCsr &A)
 // 262,144 rows on it too) a V-cycle takes 415 us at m = 1 and 918 us at m = 16
 // against 388 and 801 us; with only levels of 12 and more entries per row on
 // it, 395 and 807 us.
+// A finest level under the line gains as well (V-cycle, tiled from codes there ->
+// this): 48^3 m = 1 352 -> 234 us, m = 8 375 -> 297, m = 16 409 -> 362; channel
+// of 80 x 40 x 40 m = 1 399 -> 267, m = 16 524 -> 427; only levels of three
+// entries per row and more than two columns lose (60,000 rows of a chain, m = 6
+// 329 -> 338 us), and 20^3 at m = 13 and 15 (178 -> 183).
 constexpr int32_t kSplitMaxRows = 131072;
 // Short rows of such a level are coded all the same: the block widths whose
 // lanes do not fill a wave run the tiled product at every size, and short rows
 // gain from codes there (V-cycle of the 300 x 300 plane, levels of 90,000 to
-// 119 rows with 5 to 20 entries each: m = 3 294 us from the plain arrays, 279
-// from codes, m = 5 364 and 355, m = 7 429 and 420).  From this many entries
-// per row on, the plain arrays were as fast.
+// 119 rows with 5 to 20 entries each: m = 3 294 us from the plain arrays, 272
+// from codes, m = 5 364 and 349).  From this many entries per row on, the plain
+// arrays were as fast.
 constexpr int32_t kCodedRowNnz = 12;
 
 CsrView<double> upload_csr(mrhs_amg_s *H, const amg::HostCsr &C, const std::vector<double> *vals, int32_t reach,

@@ -1099,8 +1099,8 @@ __device__ __forceinline__ void gspmv_tiles_pat(const CsrView<T> &A, const Op &o
 // stencil pattern (PatStencil) takes its values and offsets through scalar
 // loads, kept until the pattern changes, and its four distant rows at scalar
 // addresses; other groups gather every entry.  Measured beside pattern_pays.
-// With one block gathered there is less to save than a grid line's ends cost
-// (gspmv m = 8 513 -> 522 us, m = 1 92 -> 118).
+// With one block gathered there is less to save than a grid line's ends cost:
+// an earlier form for plain products was no faster at any width.
 template <typename T, int M, class Op>
 __device__ __forceinline__ void gspmv_near_pat(const CsrView<T> &A, const Op &op,
                                                Acc<T, Shape<T, M>::VW, Op::NDOT> &acc, const TilePlan &plan)

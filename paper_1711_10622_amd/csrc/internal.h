@@ -382,8 +382,9 @@ inline hipError_t launch_gspmv(const CsrView<T> &A, const Op &op, const RedBufs<
             // every form, so that partial dot products do not depend on the
             // form.  Else row patterns, which need no LDS, fit up to eight
             // workgroups on a CU; more than four send wide rows' tiles in
-            // flight out of an XCD's L2 (12.6M-row channel, m = 8: 533 -> 553
-            // us)
+            // flight out of an XCD's L2 (eight -> four: 2.08M rows m = 12 1.23
+            // times as fast, m = 16 1.16, 938k rows 1.10 and 1.08; 524k rows m =
+            // 16 1.03, m = 10 .95)
             if (Op::NDOT == 0) {
                 fn = reinterpret_cast<const void *>(kernel);
                 if (most == 0 && Shape<T, M>::ROW_BYTES >= 64)

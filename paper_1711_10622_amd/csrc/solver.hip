@@ -75,14 +75,17 @@ bool pair_rv(const mrhs_csr_s &A)
 }
 
 // The binary64 Jacobi iteration runs as two kernels (OpXRSigma, then
-// spmv_omega) where that was measured faster: narrow blocks on small and
-// mid-size matrices, whose iterations are bound by the kernels' latency
-// chains rather than bytes.  Per iteration (ms, three kernels -> two):
-// 524k-row channel m = 1 0.083 -> 0.061, m = 4 0.096 -> 0.086, m = 8 0.129 ->
-// 0.139; 64^3 Dirichlet m = 4 0.069 -> 0.054, m = 8 0.084 -> 0.080, m = 16
-// 0.122 -> 0.140; 12.6M-row channel slower at every m (its gathers of four
-// blocks per entry and occupancy 2 cost more than a kernel boundary).
-// MRHS_MERGE: 0 never, 1 (default) where faster, 2 always.
+// spmv_omega) for narrow blocks on small and mid-size matrices, whose iterations
+// are bound by the kernels' latency chains rather than bytes.  The lines were
+// drawn when a reduction cost twice what it does now, and per iteration (ms,
+// three kernels -> two) 524k-row channel m = 4 took 0.096 -> 0.086 and 64^3
+// Dirichlet m = 8 0.084 -> 0.080.  Now two kernels still win at m = 1 (0.0386 ->
+// 0.0360 and 0.0294 -> 0.0246), and lose inside the lines at m = 4 (0.0700 ->
+// 0.0759 and 0.0467 -> 0.0475) and m = 8 (64^3: 0.0683 -> 0.0773); beyond them
+// three win as before (m = 16 0.212 -> 0.260, 0.116 -> 0.137; 12.6M-row channel
+// at every m: gathers of four blocks per entry and occupancy 2 cost more than a
+// kernel boundary).  Moving the lines changes which workspace a solve asks for.
+// MRHS_MERGE: 0 never, 1 (default) by the rule below, 2 always.
 bool merged_iteration(int32_t n, int32_t m, uint32_t flags, const AmgDev *amg)
 {
     if ((flags & MRHS_MIXED) || amg)
