@@ -1091,14 +1091,17 @@ __device__ __forceinline__ void gspmv_tiles_pat(const CsrView<T> &A, const Op &o
 // gspmv_tiles_pat for ops that gather two blocks per entry.
 //
 // Of a stencil row's block rows, the row itself and its two neighbours lie in
-// lines the wave has just asked for, and the vector cache stalls on a request
-// to a line that is still on its way (58 % of all cycles on the 12.6M-row
-// channel, m = 16, when every entry was gathered).  So a group's own rows are
-// loaded once, one pass ahead, with the two rows beside it, and the
-// neighbours' values move between lanes.  A group whose rows all have one
-// stencil pattern (PatStencil) takes its values and offsets through scalar
-// loads, kept until the pattern changes, and its four distant rows at scalar
-// addresses; other groups gather every entry.  Measured beside pattern_pays.
+// lines the wave has just asked for.  So a group's own rows are loaded once, one
+// pass ahead, with the two rows beside it, and the neighbours' values move
+// between lanes.  A group whose rows all have one stencil pattern (PatStencil)
+// takes its values and offsets through scalar loads, kept until the pattern
+// changes, and its four distant rows at scalar addresses; other groups gather
+// every entry.  Timings beside pattern_pays.  Counters on the 12.6M-row channel,
+// m = 16, codes -> this: 1790 -> 1640 us, 90 -> 85 M reads of the vector caches
+// from L2, stalled on lines still on their way 54 -> 59 % of their cycles, 6.85
+// -> 8.17 GB from and to memory.  So what it saves is the staging, its barriers
+// and LDS, not requests; it fetches more rows again than the codes and runs at
+// 0.94 of the copy rate over them: bound by memory.
 // With one block gathered there is less to save than a grid line's ends cost:
 // an earlier form for plain products was no faster at any width.
 template <typename T, int M, class Op>
