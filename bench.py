@@ -797,6 +797,7 @@ def kernel_class(name):
     """'void mrhs::k_stream<double, 16, mrhs::OpXR<double, 16> >(...)' -> 'xr_update/f64/m16';
     the columns' launches of refinement ('void mrhs::k_cols<mrhs::OpColOrth>(...)') stream one
     binary64 column per workgroup row: 'gcr_orth/f64/m1'."""
+    name = name.replace("(anonymous namespace)::", "")
     mo = re.search(r"mrhs::k_cols<mrhs::(\w+)", name)
     if mo:
         return f"{OP_NAMES.get(mo.group(1), mo.group(1))}/f64/m1"

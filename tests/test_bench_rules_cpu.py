@@ -39,6 +39,9 @@ def test_every_kernel_has_a_name():
             ("void mrhs::k_gspmv_march<double, 8, mrhs::OpStore<double, 8> >(int)", "gspmv/f64/m8")):
         assert bench.kernel_class(symbol) == cls
     assert bench.kernel_class("mrhs::k_ctl_reset(mrhs::Ctl*)") == "mrhs::k_ctl_reset"
+    anonymous = "void mrhs::k_gspmv_split<double, 1, mrhs::(anonymous namespace)::OpVcSmooth<double, 1> >(int)"
+    assert bench.kernel_class(anonymous) == "vc_smooth/f64/m1"
+    assert bench.kernel_class("mrhs::(anonymous namespace)::k_to_user(double*)") == "mrhs::k_to_user"
 
 
 RESULT = {"metric": bench.METRIC, "value": 0.6345, "unit": "s/RHS", "n_gpus": 1, "steps": 20, "warmup": 5,
