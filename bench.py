@@ -325,9 +325,10 @@ def projection_step(torch, ms=(1, 16), tau=0.05, reps=20):
     return out
 
 
-def gspmv_sweep(torch, A, ms, dtypes, flush=False, reps=50, plain=False):
+def gspmv_sweep(torch, A, ms, dtypes, flush=False, reps=50, plain=False, march=False):
     """GSpMV times over block widths ``ms``; ``plain``: the handle is made
-    with MRHS_CSR_DICT=0, so the products read the index and value arrays."""
+    with MRHS_CSR_DICT=0, so the products read the index and value arrays, as
+    they do when they run as a plane march (``march``) whatever the handle."""
     import numpy as np
     import paper_1711_10622_amd as mrhs
     old = os.environ.get("MRHS_CSR_DICT")
@@ -356,7 +357,7 @@ def gspmv_sweep(torch, A, ms, dtypes, flush=False, reps=50, plain=False):
             for tag, between in runs.items():
                 us = event_times_us(torch, lambda: M.gspmv(X, out=Y), reps, 5, between)
                 med = float(np.median(us))
-                byt = M.product_bytes(m, dt) + 2 * S * m * A.n
+                byt = (4 * (A.n + 1) + (4 + S) * A.nnz if march else M.product_bytes(m, dt)) + 2 * S * m * A.n
                 gbs = byt / (med * 1e-6) / 1e9
                 rec[tag] = {"us_median": round(med, 2), "us_p10": round(float(np.percentile(us, 10)), 2),
                             "us_p90": round(float(np.percentile(us, 90)), 2), "GBps": round(gbs, 1),
@@ -387,7 +388,7 @@ def gspmv_march(torch, A):
     old = os.environ.get("MRHS_MARCH")
     os.environ["MRHS_MARCH"] = "1"
     try:
-        return gspmv_sweep(torch, A, [1, 8, 16], ("f64", "f32"), reps=20)
+        return gspmv_sweep(torch, A, [1, 8, 16], ("f64", "f32"), reps=20, march=True)
     finally:
         if old is None:
             os.environ.pop("MRHS_MARCH", None)
